@@ -21,17 +21,6 @@
 
 namespace pdhcg {
 
-// a value every lane holds identically, moved to scalar registers
-__device__ __forceinline__ double uniform(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll));
-    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
-__device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
 // Sum (bit j of MAXMASK clear) or max (bit set) of NR values over the
 // workgroup, in a fixed order; the result lands in every thread.
 template <int NR, unsigned MAXMASK, int NT>
@@ -716,8 +705,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE))) void 
         __syncthreads();
         int b = uniform_int(s_b);
         __syncthreads();
-        if (b >= B.count) return;
-        if (B.order != nullptr) b = uniform_int(B.order[b]);
+        if (b >= B.rest_count) return;
+        if (B.rest_list != nullptr) b = uniform_int(B.rest_list[b]);
         batch_solve_one<NT, LDSN, F32, C16>(B, P, b, lds, sbuf);
     }
 }
@@ -742,7 +731,7 @@ hipError_t norm_shape(const BatchDev& B, const int* rowoff, const int* coloff, c
                       const double* tval, const int* sel, double tol, long long max_iter, double* v,
                       double* w, double* u, double* out, int grid, hipStream_t s)
 {
-    k_batch_norm<NT, LDSN><<<grid, NT, 0, s>>>(B.count, B.queue, B.order, rowoff, coloff, mrp, mcol, mval,
+    k_batch_norm<NT, LDSN><<<grid, NT, 0, s>>>(B.rest_count, B.queue, B.rest_list, rowoff, coloff, mrp, mcol, mval,
                                                trp, tcol, tval, sel, tol, max_iter, v, w, u, out);
     return hipGetLastError();
 }
@@ -805,7 +794,8 @@ hipError_t launch_batch_norm(const BatchDev& B, int shape, const int* rowoff, co
                              double tol, long long max_iter, double* v, double* w, double* u,
                              double* out, hipStream_t s)
 {
-    const int grid = batch_grid(shape, 2, B.count);
+    if (B.rest_count < 1) return hipSuccess;
+    const int grid = batch_grid(shape, 2, B.rest_count);
     int k = 0;
 #define PDHCG_SHAPE_NORM(T_, L_, W_) \
     if (k++ == shape) return norm_shape<T_, L_, W_>(B, rowoff, coloff, mrp, mcol, mval, trp, tcol, tval, sel, tol, max_iter, v, w, u, out, grid, s);
@@ -817,7 +807,8 @@ hipError_t launch_batch_norm(const BatchDev& B, int shape, const int* rowoff, co
 hipError_t launch_batch_solve(const BatchDev& B, const BatchParams& P, int shape, hipStream_t s)
 {
     const bool f32 = B.aval32 != nullptr;
-    const int grid = batch_grid(shape, f32 ? 1 : 0, B.count);
+    if (B.rest_count < 1) return hipSuccess;
+    const int grid = batch_grid(shape, f32 ? 1 : 0, B.rest_count);
     int k = 0;
 #define PDHCG_SHAPE_SOLVE(T_, L_, W_) \
     if (k++ == shape) return f32 ? solve_shape<T_, L_, W_, true>(B, P, grid, s) : solve_shape<T_, L_, W_, false>(B, P, grid, s);

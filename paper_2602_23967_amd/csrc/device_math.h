@@ -9,6 +9,17 @@
 
 namespace pdhcg {
 
+// a value every lane holds identically, moved to scalar registers
+__device__ __forceinline__ double uniform(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll));
+    const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+__device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 enum { R_SUM = 0, R_MAX = 1, R_MIN = 2 };
 
 __device__ __forceinline__ double rcomb(int kind, double a, double b)

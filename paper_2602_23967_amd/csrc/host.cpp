@@ -1047,8 +1047,13 @@ struct qp_batch {
     std::vector<double> norm_A;
     // launch schedule: shape (index into the compiled table) and queue order
     // (0 index order, 1 largest instance first; dorder holds that permutation)
+    // Each of the two queue orders lists the instances that the default
+    // shape gives to the kernels of closed.hip (nclosed of them) first, then
+    // the others; dorder is the second order for the kernels of other shapes,
+    // which take all instances
     int shape = pdhcg::BATCH_SHAPE_DEFAULT, order = 1;
-    const int* dorder = nullptr;
+    const int *dorder = nullptr, *dsplit[2] = {nullptr, nullptr};
+    int nclosed = 0;
     int solved = 0;
     double setup_seconds = 0.0, solve_seconds = 0.0;
 };
@@ -1288,7 +1293,7 @@ int batch_create(hipStream_t lane, int64_t count, const int64_t* var_off, const 
     double** mv[] = {&B.y, &B.ya, &B.yt, &B.ytil, &B.yref, &B.axref};
     for (double** p : mv)
         if ((rc = balloc(bt, p, (size_t)m))) return bail(rc);
-    if ((rc = balloc(bt, &B.queue, 1)) || (rc = balloc(bt, &B.out, (size_t)count))) return bail(rc);
+    if ((rc = balloc(bt, &B.queue, 2)) || (rc = balloc(bt, &B.out, (size_t)count))) return bail(rc);
     {
         // largest instance first (nonzeros of A and Q plus n + m), ties in
         // index order: a longest-processing-time-first queue, so the launch
@@ -1300,17 +1305,37 @@ int batch_create(hipStream_t lane, int64_t count, const int64_t* var_off, const 
         std::vector<int> perm(count);
         for (int64_t i = 0; i < count; ++i) perm[i] = (int)i;
         std::stable_sort(perm.begin(), perm.end(), [&](int a, int b_) { return work[a] > work[b_]; });
-        if ((rc = bupload(bt, &bt->dorder, perm.data(), perm.size()))) return bail(rc);
-        B.order = bt->dorder;
+        auto closed = [&](int i) {
+            return !qgen[i] && var_off[i + 1] - var_off[i] <= BATCH_CLOSED_MAX &&
+                   row_off[i + 1] - row_off[i] <= BATCH_CLOSED_MAX;
+        };
+        std::vector<int> lists(perm);   // dorder, then the two split orders
+        for (int64_t i = 0; i < count; ++i) lists.push_back((int)i);
+        bt->nclosed = (int)(std::stable_partition(lists.begin() + count, lists.end(), closed) - (lists.begin() + count));
+        lists.insert(lists.end(), perm.begin(), perm.end());
+        std::stable_partition(lists.begin() + 2 * count, lists.end(), closed);
+        // (a batch in the static workspace keeps its schedule: one list, so
+        // the same batches fit as with a plain order)
+        const int* dl = nullptr;
+        const size_t skip = arena ? (size_t)2 * count : 0;
+        if ((rc = bupload(bt, &dl, lists.data() + skip, lists.size() - skip))) return bail(rc);
+        bt->dorder = dl;
+        bt->dsplit[0] = arena ? dl : dl + count;
+        bt->dsplit[1] = arena ? dl : dl + 2 * count;
+        B.closed_count = bt->nclosed;
+        B.closed_list = bt->dsplit[1];
+        B.rest_count = (int)count - bt->nclosed;
+        B.rest_list = bt->dsplit[1] + bt->nclosed;
     }
 
     // per-instance scalars: ||A_i||_2 on the device, the rest here
     double* dnorm = nullptr;
     if ((rc = balloc(bt, &dnorm, (size_t)count))) return bail(rc);
     const qp_params dp = qp_params_default();
-    if (hipMemsetAsync(B.queue, 0, sizeof(int), bt->stream) != hipSuccess)
+    if (hipMemsetAsync(B.queue, 0, 2 * sizeof(int), bt->stream) != hipSuccess)
         return bail(fail(QP_ERR_DEVICE, "hipMemsetAsync failed"));
-    if (launch_batch_norm(B, BATCH_SHAPE_NORM, B.roff, B.voff, B.arp, B.acol, B.aval, B.trp, B.tcol, B.tval, nullptr,
+    if (launch_closed_norm(B, dp.power_tol, dp.power_max_iter, dnorm, bt->stream) != hipSuccess ||
+        launch_batch_norm(B, BATCH_SHAPE_NORM, B.roff, B.voff, B.arp, B.acol, B.aval, B.trp, B.tcol, B.tval, nullptr,
                           dp.power_tol, dp.power_max_iter, B.x, B.y, B.xt, dnorm, bt->stream) != hipSuccess ||
         hipStreamSynchronize(bt->stream) != hipSuccess)
         return bail(fail(QP_ERR_DEVICE, "norm kernel failed"));
@@ -1400,8 +1425,15 @@ int batch_launch(qp_batch* bt, const qp_params* params)
     P.gamma_inner = p.gamma_inner; P.eps_min = p.eps_min; P.eps_fixed = p.eps_inner_fixed;
     P.mprgp_gamma = p.mprgp_gamma; P.abar_scale = p.mprgp_abar_scale; P.max_inner = p.max_inner;
     bt->t_launch = now_s();
-    HIPCHK(hipMemsetAsync(bt->B.queue, 0, sizeof(int), bt->stream));
-    bt->B.order = bt->order ? bt->dorder : nullptr;
+    HIPCHK(hipMemsetAsync(bt->B.queue, 0, 2 * sizeof(int), bt->stream));
+    // The default shape's small closed-form instances have kernels of their
+    // own; an instance's route never depends on the others in the batch.
+    const int nc = bt->shape == BATCH_SHAPE_DEFAULT ? bt->nclosed : 0;
+    bt->B.closed_count = nc;
+    bt->B.closed_list = bt->dsplit[bt->order];
+    bt->B.rest_count = (int)bt->count - nc;
+    bt->B.rest_list = nc ? bt->dsplit[bt->order] + nc : (bt->order ? bt->dorder : nullptr);
+    HIPCHK(launch_closed_solve(bt->B, P, bt->stream));
     HIPCHK(launch_batch_solve(bt->B, P, bt->shape, bt->stream));
     if (bt->done) HIPCHK(hipEventRecord(bt->done, bt->stream));
     return 0;
