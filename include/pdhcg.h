@@ -133,7 +133,9 @@ typedef struct {
     double setup_seconds;      /* wall time of qp_create */
     double fam_ms[QP_NFAM];    /* summed device time of the timed launches */
     int64_t fam_timed[QP_NFAM];/* number of timed launches */
-    int64_t fam_launches[QP_NFAM]; /* number of launches */
+    int64_t fam_launches[QP_NFAM]; /* number of launches (a solve of a non-diagonal Q whose
+                                  iterations run in one launch up to the next check, which
+                                  timing = 0 allows, launches none of the families) */
     int64_t spmv_hp_active;    /* QP_FAM_SPMV_HP launches that ran (the rest found the
                                   inner solve already stopped and returned at once) */
 } qp_info;

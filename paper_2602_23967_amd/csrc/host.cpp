@@ -47,6 +47,7 @@ struct qp_handle {
     int has_unbounded_x = 0;
     int qkind = 0;   // 0 none, 1 diagonal, 2 general
     double setup_seconds = 0.0;
+    CoopDev coop;    // coop.ns > 0: solves run in the kernel of coop.hip
     // timing
     std::vector<EventPair> ev_pool;
     size_t ev_used = 0;
@@ -227,6 +228,96 @@ int upload_csr(qp_handle* h, CsrDev& M, int64_t rows, int64_t cols, const int64_
     return 0;
 }
 
+// Slices of a CSR for coop.hip: whole rows, at most `threads` of them with at
+// most COOP_EPT entries per thread.
+std::vector<BlkDesc> coop_slices(int64_t rows, const int64_t* rp, int threads)
+{
+    std::vector<BlkDesc> s;
+    for (int64_t r = 0; r < rows;) {
+        const int64_t a = r;
+        while (r < rows && r - a < threads && rp[r + 1] - rp[a] <= (int64_t)COOP_EPT * threads) ++r;
+        s.push_back({(int)a, (int)(r - a), (int)rp[a], (int)rp[r], 0, 0, 0, 0});
+    }
+    return s;
+}
+
+// lanes that the row-block products (kernels.hip) sum each row with
+std::vector<unsigned char> row_lanes(int64_t rows, const int64_t* rp)
+{
+    std::vector<BlkDesc> blk;
+    int nlr = 0, nseg = 0;
+    build_plan(rows, rp, blk, nlr, nseg);
+    std::vector<unsigned char> g(rows, 1);
+    for (const BlkDesc& b : blk) {
+        int lanes = 64;
+        while (lanes > 1 && lanes * b.nrows > TPB) lanes >>= 1;
+        for (int r = 0; r < b.nrows; ++r) g[b.row0 + r] = (unsigned char)lanes;
+    }
+    return g;
+}
+
+int64_t longest_row(int64_t rows, const int64_t* rp)
+{
+    int64_t l = 0;
+    for (int64_t i = 0; i < rows; ++i) l = std::max(l, rp[i + 1] - rp[i]);
+    return l;
+}
+
+// prepares the one-launch iteration where the problem fits it (coop.ns > 0)
+int coop_create(qp_handle* h, const int64_t* qp, const int64_t* ap, const int64_t* tp)
+{
+    const DevState& S = h->S;
+    const int64_t n = h->n, m = h->m;
+    if (h->qkind != 2 || S.k > 0 || S.Q.nparts > 1 || S.A.nparts > 1 || S.AT.nparts > 1) return 0;
+    if (longest_row(n, qp) > COOP_ROW || longest_row(m, ap) > COOP_ROW || longest_row(n, tp) > COOP_COL) return 0;
+    int dev = 0, cus = 0;
+    HIPCHK(hipGetDevice(&dev));
+    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    // Slices of 256 rows up to 128 of them, then of 512: every workgroup reads
+    // every slice's words in a round (random QPs, 128 iterations, slices of
+    // 256 and of 512: n = 3000 13.2 and 17.0 ms, n = 20,011 23.4 and 24.1 ms
+    // with 108 and 54 slices, n = 50,000 56.3 and 38.5 ms with 270 and 135).
+    int threads = 256;
+    std::vector<BlkDesc> q = coop_slices(n, qp, threads);
+    if ((int)q.size() > 128) q = coop_slices(n, qp, threads = 512);
+    // At most one slice per compute unit, whose entries then stay in
+    // registers: at n = 50,000 a solve took 80.6 ms launch by launch and takes
+    // 38.5, but at n = 200,003 (391 slices) an inner solve took 2.16 and 2.22.
+    if ((int)q.size() > cus) return 0;
+    const std::vector<BlkDesc> a = coop_slices(m, ap, threads);
+    const std::vector<unsigned char> ql = row_lanes(n, qp), al = row_lanes(m, ap), tl = row_lanes(n, tp);
+    CoopDev D;
+    D.ns = (int)q.size();
+    D.nsa = (int)a.size();
+    D.full = std::min(std::max(D.ns, D.nsa), cus);
+    D.threads = threads;
+    BlkDesc *dq, *da;
+    unsigned char *dql, *dal, *dtl;
+    int rc;
+    if ((rc = upload(h, &dq, q.data(), q.size())) || (rc = upload(h, &da, a.data(), a.size())) ||
+        (rc = upload(h, &dql, ql.data(), ql.size())) || (rc = upload(h, &dal, al.data(), al.size())) ||
+        (rc = upload(h, &dtl, tl.data(), tl.size())) || (rc = dalloc(h, &D.ex, (size_t)2 * n)) ||
+        (rc = dalloc(h, &D.ey, (size_t)m)) || (rc = dalloc(h, &D.slots, (size_t)16 * (D.ns + D.nsa))) ||
+        (rc = dalloc(h, &D.reg, 4)))
+        return rc;
+    D.qblk = dq; D.ablk = da; D.qlanes = dql; D.alanes = dal; D.tlanes = dtl;
+    D.aslots = D.slots + (size_t)16 * D.ns;
+    h->coop = D;
+    return 0;
+}
+
+// one launch of coop.hip's kernel; `done`: the iterations it made
+int coop_run(qp_handle* h, const CoopRun& R, int* done)
+{
+    h->hstat[0] = 0;
+    HIPCHK(launch_coop(h->S, h->coop, R, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+    const unsigned long long w = *(volatile unsigned long long*)h->hstat;
+    *done = (int)(w >> 1);
+    if ((w & 1ull) || *done < 1) return fail(QP_ERR_DEVICE, "a workgroup of the iteration did not answer (internal error)");
+    return 0;
+}
+
 hipStream_t stream_of(const qp_handle* h) { return h->stream; }
 
 // power-iteration estimate of ||M||_2 through M'M (Mt = M' as a CSR),
@@ -373,6 +464,8 @@ int create_impl(int64_t n, int64_t m, const int64_t* Qp, const int32_t* Qj, cons
         if ((rc = upload_csr(h, S.R, k, n, Rp, Rj, Rv))) return bail(rc);
     } else {
         if ((rc = upload_csr(h, S.Q, n, n, Qp ? Qp : q_empty.data(), Qj, Qv))) return bail(rc);
+        std::vector<int64_t> a_empty(m + 1, 0);
+        if ((rc = coop_create(h, Qp ? Qp : q_empty.data(), Ap ? Ap : a_empty.data(), tp.data()))) return bail(rc);
     }
 
     std::vector<double> lcv(m), ucv(m);
@@ -771,7 +864,8 @@ int qp_solve_ex(qp_handle* h, const qp_params* params)
     const double t0 = now_s();
     if (int rc = set_precision(h, p.precision)) return rc;
     // inner steps per graph launch (eager launches when timing kernel families)
-    const int K = (p.timing > 0 || S.qdiag) ? 0 : p.graph_steps;
+    const bool coop = h->coop.ns > 0 && p.timing == 0 && p.max_inner <= COOP_INNER;
+    const int K = (p.timing > 0 || S.qdiag || coop) ? 0 : p.graph_steps;
     if (K > 0)
         if (int rc = ensure_inner_graph(h, K)) return rc;
 
@@ -837,6 +931,21 @@ int qp_solve_ex(qp_handle* h, const qp_params* params)
         if (k >= p.max_iter) {
             status = QP_ITERATION_LIMIT;
             break;
+        }
+        if (coop) {
+            // whole iterations up to the next check
+            CoopRun R;
+            R.k = k;
+            R.t = t_round;
+            R.check_every = p.check_every;
+            R.max_iter = p.max_iter;
+            R.iters = (int)std::min<int64_t>({(int64_t)COOP_ITERS, p.check_every - k % p.check_every, p.max_iter - k});
+            R.exact = k % p.check_every == 0;
+            int done = 0;
+            if (int rc = coop_run(h, R, &done)) return rc;
+            k += done;
+            t_round += done;
+            continue;
         }
         const int next_check = ((k + 1) % p.check_every == 0) || (k + 1 >= p.max_iter);
         // the movement norms and certificate pieces are read only at the
@@ -997,9 +1106,17 @@ int qp_subproblem(qp_handle* h, double tau, const double* rhs, double* x, double
     HIPCHK(hipMemcpyAsync(S.xt, x, sizeof(double) * h->n, hipMemcpyDeviceToDevice, s));
     HIPCHK(launch_clip(S, S.xt, s));
     HIPCHK(hipStreamSynchronize(s));
-    h->hstat[0] = 0;
-    long long gseq = 1;
-    int rc = inner_solve(h, gseq, 2, true, 0);
+    int rc = 0;
+    if (h->coop.ns > 0 && max_inner <= COOP_INNER) {
+        CoopRun R;
+        R.iters = R.exact = R.sub = 1;
+        int done = 0;
+        rc = coop_run(h, R, &done);
+    } else {
+        h->hstat[0] = 0;
+        long long gseq = 1;
+        rc = inner_solve(h, gseq, 2, true, 0);
+    }
     if (rc) return rc;
     HIPCHK(hipMemcpyAsync(x, S.xt, sizeof(double) * h->n, hipMemcpyDeviceToDevice, s));
     HIPCHK(hipStreamSynchronize(s));

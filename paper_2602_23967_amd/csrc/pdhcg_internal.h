@@ -199,6 +199,33 @@ hipError_t launch_dot(const DevState& S, const double* a, const double* b, int l
 
 int vec_grid(long long len);
 
+// ---- one problem's iterations in one launch (coop.hip) -------------------------
+
+constexpr int COOP_EPT = 8;          // matrix entries per thread and slice at most
+constexpr int COOP_ROW = 256;        // entries of a row of Q and A at most (one thread sums it)
+constexpr int COOP_COL = 64;         // entries of a column of A at most
+constexpr int COOP_ITERS = 256;      // iterations of a launch at most
+constexpr int COOP_INNER = 100000;   // inner steps per iteration at most (bounds a launch's time)
+struct CoopDev {
+    int ns = 0, nsa = 0;               // slices of the variables (rows of Q) and of the rows of A
+    int full = 0, threads = 0;         // workgroups of a launch, threads of each
+    const BlkDesc *qblk = nullptr, *ablk = nullptr;   // the slices: rows and entries (whole rows)
+    // lanes that the row-block products sum each row of Q, A and A' with
+    const unsigned char *qlanes = nullptr, *alanes = nullptr, *tlanes = nullptr;
+    double *ex = nullptr, *ey = nullptr;              // exchange: two doubles per variable, one per row
+    unsigned long long *slots = nullptr, *aslots = nullptr;   // 2 x 8 words per slice; aslots follow slots
+    int* reg = nullptr;                // workgroups started, workgroups taking part
+};
+struct CoopRun {
+    long long k = 0, t = 0;            // iterations done, and those of the round
+    long long check_every = 0, max_iter = 0;
+    int iters = 0;                     // iterations of this launch at most
+    int exact = 0;                     // the first gradient is formed with a product with Q
+    int sub = 0;                       // one subproblem only: rhs given, no outer step
+};
+// posts the iterations done in the status word (flag set: a wait gave up)
+hipError_t launch_coop(const DevState& S, const CoopDev& D, const CoopRun& R, hipStream_t s);
+
 // ---- batched solve of many QPs with diagonal Q (batch.hip) ----------------------
 
 // launch shape of the batched kernels: threads per workgroup (one instance
