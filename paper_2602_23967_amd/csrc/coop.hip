@@ -28,9 +28,11 @@
 // that came within REG_WAIT_US): nobody waits for a workgroup that has not
 // started, so kernels of other streams cannot block the group, and the
 // result does not depend on W.
+//
+// FP64 only.  The FP64 sums differ from the launch-by-launch path's in their
+// last bits, which moves a solve's result by 1e-15; in mixed precision such a
+// bit can turn the FP32 rounding of an operand, and results moved by 1e-8.
 #include <math.h>
-
-#include <type_traits>
 
 #include "device_math.h"
 #include "pdhcg_internal.h"
@@ -57,14 +59,6 @@ __device__ __forceinline__ double peer_load(const double* p)
 __device__ __forceinline__ void peer_store(double* p, double v)
 {
     agent_store(reinterpret_cast<u64*>(p), (u64)__double_as_longlong(v));
-}
-__device__ __forceinline__ float peer_load(const float* p)
-{
-    return __uint_as_float(__hip_atomic_load(reinterpret_cast<const unsigned*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
-__device__ __forceinline__ void peer_store(float* p, float v)
-{
-    __hip_atomic_store(reinterpret_cast<unsigned*>(p), __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // the thread's own stores have reached memory
 __device__ __forceinline__ void stores_done()
@@ -149,52 +143,24 @@ struct Group {
     }
 };
 
-// Sum of term(i), i in [a, b), in the order that G lanes of the row-block
-// products take (kernels.hip: lane l sums terms a + l, a + l + G, ..., then a
-// butterfly from the farthest lanes), so that an FP32 sum has its bits.
-template <class V, class F>
-__device__ __forceinline__ V lane_sum(int a, int b, int G, F term)
+// sum of term(i), i in [a, b), in order, four terms in flight
+template <class F>
+__device__ __forceinline__ double row_sum(int a, int b, F term)
 {
 #pragma clang fp contract(off)
-    if (G == 1) {
-        V s = V(0);
-        int i = a;
-        for (; i + 4 <= b; i += 4) {
-            const V t0 = term(i), t1 = term(i + 1), t2 = term(i + 2), t3 = term(i + 3);
-            s += t0; s += t1; s += t2; s += t3;
-        }
-        for (; i < b; ++i) s += term(i);
-        return s;
+    double s = 0.0;
+    int i = a;
+    for (; i + 4 <= b; i += 4) {
+        const double t0 = term(i), t1 = term(i + 1), t2 = term(i + 2), t3 = term(i + 3);
+        s += t0; s += t1; s += t2; s += t3;
     }
-    V stk[6] = {V(0), V(0), V(0), V(0), V(0), V(0)};
-    V res = V(0);
-    int bits = 0;
-    while ((1 << bits) < G) ++bits;
-    for (int n = 0; n < G; ++n) {
-        const int l = (int)(__brev((unsigned)n) >> (32 - bits));
-        V s = V(0);
-        for (int i = a + l; i < b; i += G) s += term(i);
-        bool put = false;
-#pragma unroll
-        for (int d = 0; d < 6; ++d) {
-            if (!put) {
-                if ((n >> d) & 1) {
-                    s = stk[d] + s;
-                } else {
-                    stk[d] = s;
-                    put = true;
-                }
-            }
-        }
-        res = s;
-    }
-    return res;
+    for (; i < b; ++i) s += term(i);
+    return s;
 }
 
-template <int T, bool F32>
+template <int T>
 __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
 {
-    typedef typename std::conditional<F32, float, double>::type V;
     constexpr int EPT = COOP_EPT;
     __shared__ double prod[EPT * T];
     __shared__ double red[4 * (T / 64)];
@@ -250,12 +216,9 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
 
     double* const e0 = D.ex;            // phi (or beta), or x_bar
     double* const e1 = D.ex + S.n;      // the last direction, or x_T
-    float* const xb32 = reinterpret_cast<float*>(e0);
-    float* const y32 = reinterpret_cast<float*>(D.ey);
 
     int cj[EPT];
     double av[EPT];
-    float av32[EPT];
     BlkDesc qb{0, 0, 0, 0, 0, 0, 0, 0};
     int row = 0, ra = 0, rb = 0, own = 0;
     // slice s: its block, the thread's row and the block's entries
@@ -272,7 +235,6 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
             const bool in = q < cnt;
             cj[i] = in ? S.Q.col[qb.k0 + q] : -1;
             av[i] = in ? S.Q.val[qb.k0 + q] : 0.0;
-            if constexpr (F32) av32[i] = in ? S.Q.val32[qb.k0 + q] : 0.0f;
         }
     };
     if (one && G.me < NS) enter(G.me);   // rows of A alone can make more workgroups than Q has slices
@@ -289,26 +251,10 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
             if (cj[i] >= 0) prod[tid + i * T] = av[i] * x[i];
         __syncthreads();
         double s = 0.0;
-        if (own) s = lane_sum<double>(ra, rb, 1, [&](int i) { return prod[i]; });
+        if (own) s = row_sum(ra, rb, [&](int i) { return prod[i]; });
         __syncthreads();
         return s;
     };
-    auto product32 = [&](auto xop) __attribute__((always_inline)) -> double {
-#pragma clang fp contract(off)
-        float* p32 = reinterpret_cast<float*>(prod);
-        double x[EPT];
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) x[i] = cj[i] >= 0 ? xop(cj[i]) : 0.0;
-#pragma unroll
-        for (int i = 0; i < EPT; ++i)
-            if (cj[i] >= 0) p32[tid + i * T] = av32[i] * (float)x[i];
-        __syncthreads();
-        float s = 0.0f;
-        if (own) s = lane_sum<float>(ra, rb, D.qlanes[row], [&](int i) { return p32[i]; });
-        __syncthreads();
-        return (double)s;
-    };
-
     auto qslots = [&]() { return D.slots + (size_t)(G.tag & 1) * 8 * NS; };
 
     for (int iter = 0; iter < iters; ++iter) {
@@ -331,17 +277,9 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
                     r = S.rhs[i];
                 } else {
                     const int qa = S.AT.rowptr[i], qe = S.AT.rowptr[i + 1];
-                    double aty;
-                    if constexpr (F32) {
-                        const float f = iter == 0
-                            ? lane_sum<float>(qa, qe, D.tlanes[i], [&](int q) { return S.AT.val32[q] * S.dy32[S.AT.col[q]]; })
-                            : lane_sum<float>(qa, qe, D.tlanes[i], [&](int q) { return S.AT.val32[q] * peer_load(&y32[S.AT.col[q]]); });
-                        aty = (double)f + S.atyref[i];
-                    } else {
-                        aty = iter == 0
-                            ? lane_sum<double>(qa, qe, 1, [&](int q) { return S.AT.val[q] * S.y[S.AT.col[q]]; })
-                            : lane_sum<double>(qa, qe, 1, [&](int q) { return S.AT.val[q] * peer_load(&D.ey[S.AT.col[q]]); });
-                    }
+                    const double aty = iter == 0
+                        ? row_sum(qa, qe, [&](int q) { return S.AT.val[q] * S.y[S.AT.col[q]]; })
+                        : row_sum(qa, qe, [&](int q) { return S.AT.val[q] * peer_load(&D.ey[S.AT.col[q]]); });
                     r = S.x[i] * it - S.c[i] - aty;
                 }
                 const double g = exact ? qx + it * xti - r : S.g[i] + (S.rhs[i] - r) + xti * (it - g_it);
@@ -386,9 +324,7 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
                     const double f = peer_load(&e0[j]);
                     return conj ? __builtin_fma(-gam, peer_load(&e1[j]), f) : f;
                 };
-                double h;
-                if constexpr (F32) h = product32(dir);
-                else h = product(dir);
+                double h = product(dir);
                 if (own) {
                     const int i = row;
                     const double l = S.lv[i], u = S.uv[i], xi = S.xt[i], gi = S.g[i];
@@ -482,8 +418,7 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
                 const int i = row;
                 const double xti = S.xt[i], xi = S.x[i];
                 const double xb = 2.0 * xti - xi;
-                if constexpr (F32) peer_store(&xb32[i], (float)(xb - S.xref[i]));
-                else peer_store(&e0[i], xb);
+                peer_store(&e0[i], xb);
                 const double dx = xti - xi;
                 a[0] = dx * dx;
                 S.x[i] = halpern ? w * ((1.0 + th) * xti - th * xi) + wa * S.xa[i] : xti;
@@ -513,40 +448,25 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
             double a[4] = {0.0, 0.0, 0.0, 0.0};
             {
 #pragma clang fp contract(off)
-                float* p32 = reinterpret_cast<float*>(prod);
                 int aj[EPT];
-                V pv[EPT];
+                double pv[EPT], xv[EPT];
 #pragma unroll
                 for (int i = 0; i < EPT; ++i) {
                     const int q = tid + i * T;
                     aj[i] = q < cnt ? S.A.col[ab.k0 + q] : -1;
-                    if constexpr (F32) pv[i] = q < cnt ? S.A.val32[ab.k0 + q] : 0.0f;
-                    else pv[i] = q < cnt ? S.A.val[ab.k0 + q] : 0.0;
-                }
-                V xv[EPT];
-#pragma unroll
-                for (int i = 0; i < EPT; ++i) {
-                    if constexpr (F32) xv[i] = aj[i] >= 0 ? peer_load(&xb32[aj[i]]) : 0.0f;
-                    else xv[i] = aj[i] >= 0 ? peer_load(&e0[aj[i]]) : 0.0;
+                    pv[i] = q < cnt ? S.A.val[ab.k0 + q] : 0.0;
                 }
 #pragma unroll
-                for (int i = 0; i < EPT; ++i) {
-                    if (aj[i] < 0) continue;
-                    if constexpr (F32) p32[tid + i * T] = pv[i] * xv[i];
-                    else prod[tid + i * T] = pv[i] * xv[i];
-                }
+                for (int i = 0; i < EPT; ++i) xv[i] = aj[i] >= 0 ? peer_load(&e0[aj[i]]) : 0.0;
+#pragma unroll
+                for (int i = 0; i < EPT; ++i)
+                    if (aj[i] >= 0) prod[tid + i * T] = pv[i] * xv[i];
             }
             __syncthreads();
             if (tid < ab.nrows) {
                 const int i = ab.row0 + tid;
                 const int qa = S.A.rowptr[i] - ab.k0, qe = S.A.rowptr[i + 1] - ab.k0;
-                double ax;
-                if constexpr (F32) {
-                    float* p32 = reinterpret_cast<float*>(prod);
-                    ax = (double)lane_sum<float>(qa, qe, D.alanes[i], [&](int q) { return p32[q]; }) + S.axref[i];
-                } else {
-                    ax = lane_sum<double>(qa, qe, 1, [&](int q) { return prod[q]; });
-                }
+                const double ax = row_sum(qa, qe, [&](int q) { return prod[q]; });
                 const double yi = S.y[i], l = S.lc[i], u = S.uc[i];
                 const double vv = yi / sigma + ax;
                 const double yti = sigma * (vv - clampd(vv, l, u));
@@ -555,13 +475,7 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
                 a[0] = dy * dy;
                 S.yt[i] = yti;
                 S.y[i] = yn;
-                if constexpr (F32) {
-                    const float f = (float)(yn - S.yref[i]);
-                    S.dy32[i] = f;
-                    peer_store(&y32[i], f);
-                } else {
-                    peer_store(&D.ey[i], yn);
-                }
+                peer_store(&D.ey[i], yn);
                 if (store) {
                     const double yy = projY(dy, l, u);
                     S.ytil[i] = yy;
@@ -621,13 +535,8 @@ hipError_t launch_coop(const DevState& S, const CoopDev& D, const CoopRun& R, hi
     const long long words = 16ll * (D.ns + D.nsa);   // both parities of both slot arrays (one allocation)
     k_coop_begin<<<(int)((words + 255) / 256), 256, 0, s>>>(D, words);
     const int grid = D.full;
-    if (D.threads == 256) {
-        if (S.mixed) k_coop<256, true><<<grid, 256, 0, s>>>(S, D, R);
-        else k_coop<256, false><<<grid, 256, 0, s>>>(S, D, R);
-    } else {
-        if (S.mixed) k_coop<512, true><<<grid, 512, 0, s>>>(S, D, R);
-        else k_coop<512, false><<<grid, 512, 0, s>>>(S, D, R);
-    }
+    if (D.threads == 256) k_coop<256><<<grid, 256, 0, s>>>(S, D, R);
+    else k_coop<512><<<grid, 512, 0, s>>>(S, D, R);
     return hipGetLastError();
 }
 

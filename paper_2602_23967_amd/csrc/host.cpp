@@ -241,21 +241,6 @@ std::vector<BlkDesc> coop_slices(int64_t rows, const int64_t* rp, int threads)
     return s;
 }
 
-// lanes that the row-block products (kernels.hip) sum each row with
-std::vector<unsigned char> row_lanes(int64_t rows, const int64_t* rp)
-{
-    std::vector<BlkDesc> blk;
-    int nlr = 0, nseg = 0;
-    build_plan(rows, rp, blk, nlr, nseg);
-    std::vector<unsigned char> g(rows, 1);
-    for (const BlkDesc& b : blk) {
-        int lanes = 64;
-        while (lanes > 1 && lanes * b.nrows > TPB) lanes >>= 1;
-        for (int r = 0; r < b.nrows; ++r) g[b.row0 + r] = (unsigned char)lanes;
-    }
-    return g;
-}
-
 int64_t longest_row(int64_t rows, const int64_t* rp)
 {
     int64_t l = 0;
@@ -285,22 +270,20 @@ int coop_create(qp_handle* h, const int64_t* qp, const int64_t* ap, const int64_
     // 38.5, but at n = 200,003 (391 slices) an inner solve took 2.16 and 2.22.
     if ((int)q.size() > cus) return 0;
     const std::vector<BlkDesc> a = coop_slices(m, ap, threads);
-    const std::vector<unsigned char> ql = row_lanes(n, qp), al = row_lanes(m, ap), tl = row_lanes(n, tp);
     CoopDev D;
     D.ns = (int)q.size();
     D.nsa = (int)a.size();
     D.full = std::min(std::max(D.ns, D.nsa), cus);
     D.threads = threads;
     BlkDesc *dq, *da;
-    unsigned char *dql, *dal, *dtl;
     int rc;
     if ((rc = upload(h, &dq, q.data(), q.size())) || (rc = upload(h, &da, a.data(), a.size())) ||
-        (rc = upload(h, &dql, ql.data(), ql.size())) || (rc = upload(h, &dal, al.data(), al.size())) ||
-        (rc = upload(h, &dtl, tl.data(), tl.size())) || (rc = dalloc(h, &D.ex, (size_t)2 * n)) ||
+        (rc = dalloc(h, &D.ex, (size_t)2 * n)) ||
         (rc = dalloc(h, &D.ey, (size_t)m)) || (rc = dalloc(h, &D.slots, (size_t)16 * (D.ns + D.nsa))) ||
         (rc = dalloc(h, &D.reg, 4)))
         return rc;
-    D.qblk = dq; D.ablk = da; D.qlanes = dql; D.alanes = dal; D.tlanes = dtl;
+    D.qblk = dq;
+    D.ablk = da;
     D.aslots = D.slots + (size_t)16 * D.ns;
     h->coop = D;
     return 0;
@@ -864,7 +847,7 @@ int qp_solve_ex(qp_handle* h, const qp_params* params)
     const double t0 = now_s();
     if (int rc = set_precision(h, p.precision)) return rc;
     // inner steps per graph launch (eager launches when timing kernel families)
-    const bool coop = h->coop.ns > 0 && p.timing == 0 && p.max_inner <= COOP_INNER;
+    const bool coop = h->coop.ns > 0 && p.timing == 0 && p.max_inner <= COOP_INNER && p.precision == QP_PRECISION_FP64;
     const int K = (p.timing > 0 || S.qdiag || coop) ? 0 : p.graph_steps;
     if (K > 0)
         if (int rc = ensure_inner_graph(h, K)) return rc;

@@ -210,8 +210,6 @@ struct CoopDev {
     int ns = 0, nsa = 0;               // slices of the variables (rows of Q) and of the rows of A
     int full = 0, threads = 0;         // workgroups of a launch, threads of each
     const BlkDesc *qblk = nullptr, *ablk = nullptr;   // the slices: rows and entries (whole rows)
-    // lanes that the row-block products sum each row of Q, A and A' with
-    const unsigned char *qlanes = nullptr, *alanes = nullptr, *tlanes = nullptr;
     double *ex = nullptr, *ey = nullptr;              // exchange: two doubles per variable, one per row
     unsigned long long *slots = nullptr, *aslots = nullptr;   // 2 x 8 words per slice; aslots follow slots
     int* reg = nullptr;                // workgroups started, workgroups taking part
