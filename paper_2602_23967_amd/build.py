@@ -12,8 +12,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libpdhcg_hip.so")
 OBJDIR = os.path.join(ROOT, "_build")
-SOURCES = [os.path.join(HERE, "csrc", f) for f in ("kernels.hip", "batch.hip", "closed.hip", "coop.hip", "calib.hip", "host.cpp",
-                                                  "serve.cpp", "noalloc.cpp", "prep.cpp")]
+SOURCES = [os.path.join(HERE, "csrc", f) for f in ("kernels.hip", "batch.hip", "closed.hip", "general.hip", "coop.hip",
+                                                   "calib.hip", "host.cpp", "serve.cpp", "noalloc.cpp", "prep.cpp")]
 
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          # no packed FP32 instructions anywhere (hipcc's host pass warns about

@@ -1150,12 +1150,12 @@ struct qp_batch {
     // launch schedule: shape (index into the compiled table) and queue order
     // (0 index order, 1 largest instance first; dorder holds that permutation)
     // Each of the two queue orders lists the instances that the default
-    // shape gives to the kernels of closed.hip (nclosed of them) first, then
-    // the others; dorder is the second order for the kernels of other shapes,
-    // which take all instances
+    // shapes give to the kernels of closed.hip (nclosed of them) and
+    // general.hip (ngeneral) first, then the others; dorder is the second
+    // order for the kernels of other shapes, which take all instances
     int shape = pdhcg::BATCH_SHAPE_DEFAULT, order = 1;
     const int *dorder = nullptr, *dsplit[2] = {nullptr, nullptr};
-    int nclosed = 0;
+    int nclosed = 0, ngeneral = 0;
     int solved = 0;
     double setup_seconds = 0.0, solve_seconds = 0.0;
     // results of the last solve already on the host: instances [i0, i1)
@@ -1403,7 +1403,7 @@ int batch_create(hipStream_t lane, int64_t count, const int64_t* var_off, const 
     double** mv[] = {&B.y, &B.ya, &B.yt, &B.ytil, &B.yref, &B.axref};
     for (double** p : mv)
         if ((rc = balloc(bt, p, (size_t)m))) return bail(rc);
-    if ((rc = balloc(bt, &B.queue, 2)) || (rc = balloc(bt, &B.out, (size_t)count))) return bail(rc);
+    if ((rc = balloc(bt, &B.queue, 3)) || (rc = balloc(bt, &B.out, (size_t)count))) return bail(rc);
     {
         // largest instance first (nonzeros of A and Q plus n + m), ties in
         // index order: a longest-processing-time-first queue, so the launch
@@ -1415,15 +1415,19 @@ int batch_create(hipStream_t lane, int64_t count, const int64_t* var_off, const 
         std::vector<int> perm(count);
         for (int64_t i = 0; i < count; ++i) perm[i] = (int)i;
         std::stable_sort(perm.begin(), perm.end(), [&](int a, int b_) { return work[a] > work[b_]; });
-        auto closed = [&](int i) {
-            return !qgen[i] && var_off[i + 1] - var_off[i] <= BATCH_CLOSED_MAX &&
-                   row_off[i + 1] - row_off[i] <= BATCH_CLOSED_MAX;
+        auto one_cu = [&](int i) {
+            return var_off[i + 1] - var_off[i] <= ONE_CU_MAX && row_off[i + 1] - row_off[i] <= ONE_CU_MAX;
         };
+        auto closed = [&](int i) { return !qgen[i] && one_cu(i); };
         std::vector<int> lists(perm);   // dorder, then the two split orders
         for (int64_t i = 0; i < count; ++i) lists.push_back((int)i);
-        bt->nclosed = (int)(std::stable_partition(lists.begin() + count, lists.end(), closed) - (lists.begin() + count));
         lists.insert(lists.end(), perm.begin(), perm.end());
-        std::stable_partition(lists.begin() + 2 * count, lists.end(), closed);
+        for (int o = 1; o <= 2; ++o) {
+            const auto first = lists.begin() + o * count, end = first + count;
+            const auto second = std::stable_partition(first, end, closed);
+            bt->nclosed = (int)(second - first);
+            bt->ngeneral = (int)(std::stable_partition(second, end, one_cu) - second);
+        }
         // (a batch in the static workspace keeps its schedule: one list, so
         // the same batches fit as with a plain order)
         const int* dl = nullptr;
@@ -1540,15 +1544,21 @@ int batch_launch(qp_batch* bt, const qp_params* params)
         bt->ahead.i0 = bt->ahead.i1 = 0;
         bt->ahead.next = 1;
     }
-    HIPCHK(hipMemsetAsync(bt->B.queue, 0, 2 * sizeof(int), bt->stream));
-    // The default shape's small closed-form instances have kernels of their
-    // own; an instance's route never depends on the others in the batch.
-    const int nc = bt->shape == BATCH_SHAPE_DEFAULT ? bt->nclosed : 0;
+    HIPCHK(hipMemsetAsync(bt->B.queue, 0, 3 * sizeof(int), bt->stream));
+    // The default shapes' small instances have kernels of their own; an
+    // instance's route never depends on the others in the batch.
+    const bool split = bt->shape == BATCH_SHAPE_DEFAULT || bt->shape == BATCH_SHAPE_GENERAL_DEFAULT;
+    const int nc = split ? bt->nclosed : 0;
+    const int ng = split && p.precision == QP_PRECISION_FP64 ? bt->ngeneral : 0;
+    const int* list = bt->dsplit[bt->order];
     bt->B.closed_count = nc;
-    bt->B.closed_list = bt->dsplit[bt->order];
-    bt->B.rest_count = (int)bt->count - nc;
-    bt->B.rest_list = nc ? bt->dsplit[bt->order] + nc : (bt->order ? bt->dorder : nullptr);
+    bt->B.closed_list = list;
+    bt->B.general_count = ng;
+    bt->B.general_list = list + nc;
+    bt->B.rest_count = (int)bt->count - nc - ng;
+    bt->B.rest_list = split ? list + nc + ng : (bt->order ? bt->dorder : nullptr);
     HIPCHK(launch_closed_solve(bt->B, P, bt->stream));
+    HIPCHK(launch_general_solve(bt->B, P, bt->stream));
     HIPCHK(launch_batch_solve(bt->B, P, bt->shape, bt->stream));
     if (bt->done) HIPCHK(hipEventRecord(bt->done, bt->stream));
     return 0;

@@ -258,11 +258,11 @@ struct BatchParams {
 
 struct BatchDev {
     int count = 0;
-    int* queue = nullptr;                       // two work counters (instances taken): rest_list, closed_list
-    // queue position -> instance, for the kernels of batch.hip and for those
-    // of closed.hip
-    int rest_count = 0, closed_count = 0;
-    const int *rest_list = nullptr, *closed_list = nullptr;
+    int* queue = nullptr;                       // work counters (instances taken): rest, closed, general
+    // queue position -> instance, for the kernels of batch.hip, closed.hip
+    // and general.hip
+    int rest_count = 0, closed_count = 0, general_count = 0;
+    const int *rest_list = nullptr, *closed_list = nullptr, *general_list = nullptr;
     const int *voff = nullptr, *roff = nullptr; // count + 1 each
     const int *arp = nullptr, *acol = nullptr;  // A, global indices
     const double* aval = nullptr;
@@ -304,10 +304,12 @@ hipError_t launch_batch_norm(const BatchDev& B, int shape, const int* rowoff, co
                              double tol, long long max_iter, double* v, double* w, double* u,
                              double* out, hipStream_t s);
 hipError_t launch_batch_solve(const BatchDev& B, const BatchParams& P, int shape, hipStream_t s);
-// the instances of closed_list (closed.hip): closed form, at most
-// BATCH_CLOSED_MAX variables and rows each
-constexpr int BATCH_CLOSED_MAX = 1024;
+// the instances of closed_list (closed.hip): closed form; and of
+// general_list (general.hip): inner solves; at most ONE_CU_MAX variables and
+// rows each
+constexpr int ONE_CU_MAX = 1024;
 hipError_t launch_closed_solve(const BatchDev& B, const BatchParams& P, hipStream_t s);
+hipError_t launch_general_solve(const BatchDev& B, const BatchParams& P, hipStream_t s);
 hipError_t launch_closed_norm(const BatchDev& B, double tol, long long max_iter, double* out, hipStream_t s);
 // dst[i] = (float)src[i]
 hipError_t launch_to_f32(const double* src, float* dst, long long len, hipStream_t s);
