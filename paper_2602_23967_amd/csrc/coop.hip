@@ -11,9 +11,10 @@
 // a round costs 1.5 us for 8 workgroups, 2.7 for 128 and 4.1 for 256
 // (measured), and the sums are the same in every workgroup, so each takes
 // the method's decisions itself.  A solve of the random QPs, launch by launch
-// and here: n = 1000 to its tolerance 247 and 97 ms, n = 20,011 for 128
-// iterations 50.1 and 24.2 ms, n = 50,000 80.6 and 38.5 ms.  What is left is
-// the rounds' latency: about 5 us each with their gathers.
+// for 128 iterations, and here: n = 3000 37.2 and 13.2 ms, n = 20,011 50.1
+// and 24.2 ms, n = 50,000 80.6 and 38.5 ms.  What is left is the rounds'
+// latency: about 5 us each with their gathers.  (general.hip takes the
+// problems that one CU holds.)
 //
 // Exchange.  Values that other workgroups read go through agent-scope relaxed
 // atomic stores and loads (performed at memory, past the XCDs' L2s, which are

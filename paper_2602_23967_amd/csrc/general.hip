@@ -4,8 +4,11 @@
 // 1024 threads that has a CU to itself, one variable and one row per thread.
 // The iteration is the general batched kernel's (batch.hip), with the
 // thread's row of Q and the inner solve's vectors in registers and A in LDS:
-// an inner step is LDS gathers and four barriers, where the general kernel
-// read Q and six vectors from memory in every step (about 30 us a step).
+// an inner step is LDS gathers and three barriers, where the general kernel
+// read Q and six vectors from memory in every step.  24 random QPs of 200 to
+// 1000 variables, 320 iterations: 76 ms there, 19.4 here, 4.6 to 5.5 us an
+// inner step with its share of the outer one.  What is left is bound by
+// instruction issue: 16 waves of some 700 instructions a step.
 //
 // The variables are dealt to the threads by the length of their row of Q,
 // longest first: a wave's product takes as long as its longest row, so in
@@ -24,45 +27,72 @@
 
 namespace pdhcg {
 
-constexpr int REG_Q = 16;            // entries of a row of Q in registers
-constexpr int REST_Q = 4096;         // places in LDS for the longer rows' other entries
+constexpr int REG_Q = ONE_CU_REG_Q;     // entries of a row of Q in registers
+constexpr int REST_Q = ONE_CU_REST_Q;   // places in LDS for the longer rows' other entries
 constexpr int LDS_ALL = 160 * 1024 / 8;
 constexpr int OP = REG_MAX + 2;      // an operand and its zero entry
 // LDS in doubles: reductions, three operands, state, the deal of the variables
 constexpr int AT_RED = 0;
 constexpr int AT_OPS = AT_RED + RED_SLOTS * WAVES;        // (the check uses the first operand's space)
 constexpr int AT_STEP = AT_OPS + 3 * OP;                  // two buffers of the step's reductions
-constexpr int AT_STATE = AT_STEP + 2 * 4 * WAVES;
+constexpr int AT_STATE = AT_STEP + 2 * 16 * WAVES;
 constexpr int AT_MISC = AT_STATE + (int)((sizeof(ClosedState) + 7) / 8);
 constexpr int AT_DEAL = AT_MISC + 16;                     // place of a variable, variable of a place (16 bits each)
 constexpr int AT_REST = AT_DEAL + 2 * REG_MAX / 4;
 constexpr int AT_A = AT_REST + REST_Q + REST_Q / 4;
 constexpr int A_PLACES = ((LDS_ALL - AT_A) * 8 / 10) & ~63;
 
-// four values over the workgroup, in every thread: sums, but the last a
-// minimum where MIN3.  One barrier; every wave reads the 16 waves' values in
-// one load and finishes the reduction in its lane crossbar.
+// v of the lane `CTRL` names, lanes without a source 0
+template <int CTRL>
+__device__ __forceinline__ double row_from(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+// sum over a row of 16 lanes, in its lane 15
+__device__ __forceinline__ double row_sum(double v)
+{
+    v += row_from<0x111>(v);
+    v += row_from<0x112>(v);
+    v += row_from<0x114>(v);
+    return v + row_from<0x118>(v);
+}
+__device__ __forceinline__ double lesser(double a, double b) { return b < a ? b : a; }
+__device__ __forceinline__ double row_min(double v)
+{
+    v = lesser(v, dpp_from<0x111, 0xf>(v, INFINITY));
+    v = lesser(v, dpp_from<0x112, 0xf>(v, INFINITY));
+    v = lesser(v, dpp_from<0x114, 0xf>(v, INFINITY));
+    return lesser(v, dpp_from<0x118, 0xf>(v, INFINITY));
+}
+
+// Four values over the workgroup, in every thread: sums, but the last a
+// minimum where MIN3.  One barrier.  The kernel is bound by instruction
+// issue (4 waves on a SIMD), so a wave reduces no further than its rows of
+// 16 lanes; then every wave reads the 64 rows' partials, 16 lanes for each
+// value.  live: the wave has a variable (otherwise its values are the
+// identities).
 template <bool MIN3>
-__device__ __forceinline__ void step_sum(double (&v)[4], double* lds)
+__device__ __forceinline__ void step_sum(double (&v)[4], bool live, double* lds)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    static_assert(WAVES == 16, "a value's waves fill a row of 16 lanes");
+    if (live) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        v[j] = wave_reduce(MIN3 && j == 3 ? R_MIN : R_SUM, v[j]);
-        if (lane == 0) lds[j * WAVES + wave] = v[j];
+        for (int j = 0; j < 4; ++j) v[j] = MIN3 && j == 3 ? row_min(v[j]) : (MIN3 && j == 2 ? 0.0 : row_sum(v[j]));
+    }
+    if ((lane & 15) == 15) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) lds[(j * WAVES + wave) * 4 + (lane >> 4)] = v[j];
     }
     __syncthreads();
-    static_assert(WAVES == 16, "a value's partials fill a row of 16 lanes");
-    double r = lds[lane];
-    const bool mn = MIN3 && lane >= 48;
-    const double id = mn ? INFINITY : 0.0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const double o = q == 0   ? dpp_from<0x111, 0xf>(r, id)
-                         : q == 1 ? dpp_from<0x112, 0xf>(r, id)
-                         : q == 2 ? dpp_from<0x114, 0xf>(r, id)
-                                  : dpp_from<0x118, 0xf>(r, id);
-        r = mn ? rcomb(R_MIN, r, o) : r + o;
+    const double *q = lds + 4 * lane, a0 = q[0], a1 = q[1], a2 = q[2], a3 = q[3];
+    double r = row_sum((a0 + a1) + (a2 + a3));
+    if constexpr (MIN3) {
+        const double mn = row_min(lesser(lesser(a0, a1), lesser(a2, a3)));
+        r = lane >= 48 ? mn : r;
     }
     const long long b = __double_as_longlong(r);
     const int lo = (int)(b & 0xffffffffll), hi = (int)(b >> 32);
@@ -120,12 +150,171 @@ __device__ __forceinline__ void fill(Share p, int a, int len, int from, const do
     }
 }
 
+// the thread's row of Q: REG_Q entries in registers (places of their columns
+// two to a word), the others in its wave's share of the LDS
+struct RowQ {
+    double v[REG_Q];
+    unsigned o[REG_Q / 2];
+    int most;            // entries of the wave's longest row
+    int base, wide;
+    const double* lv;
+    const unsigned short* lo;
+
+    __device__ __forceinline__ void load(int a, int len, const double* val, const unsigned short* c16, const int* c32,
+                                         int first, const unsigned short* deal, int zero)
+    {
+#pragma unroll
+        for (int q = 0; q < REG_Q; ++q) {
+            const bool have = q < len;
+            v[q] = have ? val[a + q] : 0.0;
+            const unsigned j = have ? deal[local_col(c16, c32, a + q, first)] : (unsigned)zero;
+            o[q / 2] = q % 2 ? o[q / 2] | (j << 16) : j;
+        }
+    }
+    // times an operand in LDS, in row order
+    __device__ __forceinline__ double dot(const double* op) const
+    {
+        double r = 0.0;
+#pragma unroll
+        for (int q = 0; q < REG_Q; q += 4) {
+            if (q < most) {
+                double g[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) g[e] = op[(o[(q + e) / 2] >> (16 * (e & 1))) & 0xffffu];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r += v[q + e] * g[e];
+            }
+        }
+        if (wide > 0) {
+            const int f = base + (threadIdx.x & 63);
+            int w = 0;
+            for (; w + 4 <= wide; w += 4) {
+                double x[4], g[4];
+                unsigned c[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { c[e] = lo[f + 64 * (w + e)]; x[e] = lv[f + 64 * (w + e)]; }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) g[e] = op[c[e]];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) r += x[e] * g[e];
+            }
+            for (; w < wide; ++w) r += lv[f + 64 * w] * op[lo[f + 64 * w]];
+        }
+        return r;
+    }
+};
+
+// The boxed CG inner solve (MPRGP) of the subproblem with right-hand side
+// rhs from x_T = xt with gradient g; st: ||g^P||^2, ||beta||^2 and phit'phi
+// there, left as they are at the end.  live: the wave has a variable.
+struct Inner {
+    double it, abar, gamma2, eps;
+    long long max_inner;
+    long long steps = 0, products = 0;
+};
+__device__ __forceinline__ void inner_solve(Inner& s, const RowQ& Q, bool on, bool live, double l, double u, double rhs,
+                                            double& xt, double& g, double (&st)[4], double* sp, double* sxt, double* redh,
+                                            double* redu)
+{
+    const int tid = threadIdx.x;
+    double p = 0.0, hp = 0.0, gam = 0.0;
+    int done = uniform_int(sqrt(st[0]) <= s.eps || s.max_inner <= 0);
+    int mode = uniform_int(st[1] <= s.gamma2 * st[2] ? DIR_PHI : DIR_BETA);
+    while (!done) {
+        if (on) {
+            const Split f = split(xt, g, l, u, s.abar);
+            p = mode == DIR_BETA ? f.beta : (mode == DIR_PHI ? f.phi : f.phi - gam * p);
+            sp[tid] = p;
+        }
+        __syncthreads();
+        double hs[4] = {0.0, 0.0, 0.0, INFINITY};   // p'Hp, g'p, -, feasible step
+        if (live) {
+            const double qp = Q.dot(sp);
+            if (on) {
+                hp = qp + s.it * p;
+                hs[0] = p * hp;
+                hs[1] = g * p;
+                if (p > 0.0 && isfinite(l)) hs[3] = (xt - l) / p;
+                else if (p < 0.0 && isfinite(u)) hs[3] = (xt - u) / p;
+            }
+        }
+        ++s.products;
+        step_sum<true>(hs, live, redh);
+        if (uniform_int(!(hs[0] > 0.0))) break;
+        const double af = hs[3] < 0.0 ? 0.0 : hs[3];
+        const double acg = hs[1] / hs[0];
+        int kind;
+        double alpha;
+        if (mode == DIR_BETA) { kind = STEP_PROP; alpha = acg < af ? acg : af; }
+        else if (acg <= af) { kind = STEP_CG; alpha = acg; }
+        else { kind = STEP_EXPAND; alpha = af; }
+        kind = uniform_int(kind);
+        alpha = uniform(alpha);
+        double us[4] = {0.0, 0.0, 0.0, 0.0};   // the same three and phi'Hp
+        if (on) {
+            xt = clampd(xt - alpha * p, l, u);
+            g = g - alpha * hp;
+            const Split f = split(xt, g, l, u, s.abar);
+            if (kind == STEP_EXPAND) {
+                xt = clampd(xt - s.abar * f.phi, l, u);
+                sxt[tid] = xt;
+            } else {
+                us[0] = f.phi * f.phi + f.beta * f.beta;
+                us[1] = f.beta * f.beta;
+                us[2] = f.phit * f.phi;
+                us[3] = f.phi * hp;
+            }
+        }
+        ++s.steps;
+        if (kind == STEP_EXPAND) {
+            __syncthreads();
+            ++s.products;
+            if (live) {
+                const double qx = Q.dot(sxt);
+                if (on) {
+                    g = qx + s.it * xt - rhs;
+                    const Split f = split(xt, g, l, u, s.abar);
+                    us[0] = f.phi * f.phi + f.beta * f.beta;
+                    us[1] = f.beta * f.beta;
+                    us[2] = f.phit * f.phi;
+                }
+            }
+        }
+        step_sum<false>(us, live, redu);
+        if (kind == STEP_CG) gam = uniform(us[3] / hs[0]);
+        st[0] = us[0];
+        done = uniform_int(sqrt(us[0]) <= s.eps || s.steps >= s.max_inner);
+        const bool prop = us[1] <= s.gamma2 * us[2];
+        mode = uniform_int(!prop ? DIR_BETA : (kind == STEP_CG ? DIR_CONJ : DIR_PHI));
+    }
+}
+
+// the deal of the variables to the threads: rows of Q by length, ties in
+// index order
+__device__ __forceinline__ void deal_rows(int n, const int* rp, int* lens, unsigned short* place, unsigned short* var)
+{
+    const int tid = threadIdx.x;
+    lens[tid] = tid < n ? rp[tid + 1] - rp[tid] : -1;
+    __syncthreads();
+    const int mine = lens[tid];
+    int r = 0;
+    for (int j = 0; j < n; ++j) {
+        const int o = lens[j];
+        r += (o > mine || (o == mine && j < tid)) ? 1 : 0;
+    }
+    if (tid < n) {
+        place[tid] = (unsigned short)r;
+        var[r] = (unsigned short)tid;
+    }
+    __syncthreads();
+}
+
 __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchParams P)
 {
     __shared__ double sh[LDS_ALL];
     double* red = sh + AT_RED;
     double* redh = sh + AT_STEP;
-    double* redu = redh + 4 * WAVES;
+    double* redu = redh + 16 * WAVES;
     double* sp = sh + AT_OPS;              // direction; x_bar
     double* sxt = sh + AT_OPS + OP;        // x_T
     double* sy = sh + AT_OPS + 2 * OP;     // y
@@ -150,30 +339,21 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
         const int v0 = in.v0, r0 = in.r0, n = in.n, m = in.m, unb = in.unb;
         const double normq = uniform(B.normq[b]);
         const bool xon = tid < n, yon = tid < m;
-        // the deal: rows of Q by length, ties in index order
-        {
-            int* lens = reinterpret_cast<int*>(sh + AT_OPS);
-            lens[tid] = xon ? B.qrp[v0 + tid + 1] - B.qrp[v0 + tid] : -1;
-            __syncthreads();
-            const int mine = lens[tid];
-            int r = 0;
-            for (int j = 0; j < n; ++j) {
-                const int o = lens[j];
-                r += (o > mine || (o == mine && j < tid)) ? 1 : 0;
-            }
-            if (xon) {
-                place[tid] = (unsigned short)r;
-                var[r] = (unsigned short)tid;
-            }
-            __syncthreads();
-        }
+        deal_rows(n, B.qrp + v0, reinterpret_cast<int*>(sh + AT_OPS), place, var);
         const int vi = v0 + (xon ? (int)var[tid] : 0), ri = r0 + (yon ? tid : 0);
         const int qa = xon ? B.qrp[vi] : 0, ql = xon ? B.qrp[vi + 1] - qa : 0;
         const int ta = xon ? B.trp[vi] : 0, tl = xon ? B.trp[vi + 1] - ta : 0;
         const int aa = yon ? B.arp[ri] : 0, al = yon ? B.arp[ri + 1] - aa : 0;
         const int qmost = longest(ql), amost = longest(al);
+        const bool live = uniform_int(tid & ~63) < n, any = uniform_int(tid & ~63) < (n > m ? n : m);
+        RowQ Q;
+        Q.most = qmost;
         const Share qs = share(qmost > REG_Q ? qmost - REG_Q : 0, REST_Q, misc + 16);
         const Share as = share(amost, A_PLACES, misc + 16);
+        Q.base = qs.base;
+        Q.wide = qs.wide;
+        Q.lv = lqv;
+        Q.lo = lqo;
         fill(qs, qa, ql, REG_Q, B.qval, B.qcol16, B.qcol, v0, place, n, lqv, lqo);
         fill(as, aa, al, 0, B.aval, B.acol16, B.acol, v0, place, n, lav, lao);
         for (int i = tid; i < 3 * OP; i += REG_MAX) sh[AT_OPS + i] = 0.0;
@@ -223,51 +403,14 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
             // The iterations to the next check (in pieces of at most 2^30);
             // the row of Q and the box are loaded here, not before the loop
             // over the checks: live across a check they would be spilled.
-            double qv[REG_Q];
-            unsigned qo[REG_Q / 2];   // places, two to a word
-#pragma unroll
-            for (int q = 0; q < REG_Q; ++q) {
-                const bool have = q < ql;
-                qv[q] = have ? B.qval[qa + q] : 0.0;
-                const unsigned j = have ? place[local_col(B.qcol16, B.qcol, qa + q, v0)] : (unsigned)n;
-                qo[q / 2] = q % 2 ? qo[q / 2] | (j << 16) : j;
-            }
+            Q.load(qa, ql, B.qval, B.qcol16, B.qcol, v0, place, n);
             const double l = xon ? B.lv[vi] : -INFINITY, u = xon ? B.uv[vi] : INFINITY;
-            // row of Q times an operand in LDS, in row order
-            auto qdot = [&](const double* op) __attribute__((always_inline)) {
-                double r = 0.0;
-#pragma unroll
-                for (int q = 0; q < REG_Q; q += 4) {
-                    if (q < qmost) {
-                        double g[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) g[e] = op[(qo[(q + e) / 2] >> (16 * (e & 1))) & 0xffffu];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) r += qv[q + e] * g[e];
-                    }
-                }
-                if (qmost > REG_Q) {
-                    const int f = qs.base + (tid & 63);
-                    int w = 0;
-                    for (; w + 4 <= qs.wide; w += 4) {
-                        double v[4], g[4];
-                        unsigned o[4];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) { o[e] = lqo[f + 64 * (w + e)]; v[e] = lqv[f + 64 * (w + e)]; }
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) g[e] = op[o[e]];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) r += v[e] * g[e];
-                    }
-                    for (; w < qs.wide; ++w) r += lqv[f + 64 * w] * op[lqo[f + 64 * w]];
-                    for (int q = REG_Q + qs.wide; q < ql; ++q)
-                        r += B.qval[qa + q] * op[place[local_col(B.qcol16, B.qcol, qa + q, v0)]];
-                }
-                return r;
-            };
             const double it = uniform(s->it), sigma = uniform(s->sigma), tau = uniform(s->tau), omega = uniform(s->omega);
-            const double abar = P.abar_scale / (normq + it);
-            const double gamma2 = P.mprgp_gamma * P.mprgp_gamma;
+            Inner cg;
+            cg.it = it;
+            cg.abar = P.abar_scale / (normq + it);
+            cg.gamma2 = P.mprgp_gamma * P.mprgp_gamma;
+            cg.max_inner = P.max_inner;
             long long left = P.check_every - k % P.check_every;
             left = left < P.max_iter - k ? left : P.max_iter - k;
             const int steps = uniform_int((int)(left < (1ll << 30) ? left : (1ll << 30)));
@@ -275,90 +418,28 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
             for (int r = 0; r < steps; ++r) {
                 const bool store = last && r + 1 == steps;
                 // right-hand side, and the gradient at x_T with a product with Q
-                double rhs = 0.0, g = 0.0, p = 0.0, hp = 0.0;
+                double rhs = 0.0, g = 0.0;
                 double st[4] = {0.0, 0.0, 0.0, 0.0};   // ||g^P||^2, ||beta||^2, phit'phi
                 {
                     double aty = 0.0;
 #pragma unroll 4
                     for (int q = 0; q < tl; ++q) aty += B.tval[ta + q] * sy[local_col(B.tcol16, B.tcol, ta + q, r0)];
-                    const double qx = qdot(sxt);
+                    const double qx = Q.dot(sxt);
                     if (xon) {
                         rhs = x * it - B.c[vi] - aty;
                         g = qx + it * xt - rhs;
-                        const Split f = split(xt, g, l, u, abar);
+                        const Split f = split(xt, g, l, u, cg.abar);
                         st[0] = f.phi * f.phi + f.beta * f.beta;
                         st[1] = f.beta * f.beta;
                         st[2] = f.phit * f.phi;
                     }
                 }
-                step_sum<false>(st, redu);
+                step_sum<false>(st, live, redu);
                 if (isinf(eps) && P.eps_fixed <= 0.0) eps = uniform(fmax(P.gamma_inner * sqrt(st[0]), P.eps_min));
-                const double eps_use = P.eps_fixed > 0.0 ? P.eps_fixed : eps;
-                long long inner = 0;
-                double gam = 0.0;
-                int done = uniform_int(sqrt(st[0]) <= eps_use || P.max_inner <= 0);
-                int mode = uniform_int(st[1] <= gamma2 * st[2] ? DIR_PHI : DIR_BETA);
-                while (!done) {
-                    if (xon) {
-                        const Split f = split(xt, g, l, u, abar);
-                        p = mode == DIR_BETA ? f.beta : (mode == DIR_PHI ? f.phi : f.phi - gam * p);
-                        sp[tid] = p;
-                    }
-                    __syncthreads();
-                    double hs[4] = {0.0, 0.0, 0.0, INFINITY};   // p'Hp, g'p, -, feasible step
-                    const double qp = qdot(sp);
-                    if (xon) {
-                        hp = qp + it * p;
-                        hs[0] = p * hp;
-                        hs[1] = g * p;
-                        if (p > 0.0 && isfinite(l)) hs[3] = (xt - l) / p;
-                        else if (p < 0.0 && isfinite(u)) hs[3] = (xt - u) / p;
-                    }
-                    step_sum<true>(hs, redh);
-                    if (uniform_int(!(hs[0] > 0.0))) break;
-                    const double af = hs[3] < 0.0 ? 0.0 : hs[3];
-                    const double acg = hs[1] / hs[0];
-                    int kind;
-                    double alpha;
-                    if (mode == DIR_BETA) { kind = STEP_PROP; alpha = acg < af ? acg : af; }
-                    else if (acg <= af) { kind = STEP_CG; alpha = acg; }
-                    else { kind = STEP_EXPAND; alpha = af; }
-                    kind = uniform_int(kind);
-                    alpha = uniform(alpha);
-                    double us[4] = {0.0, 0.0, 0.0, 0.0};   // the same three and phi'Hp
-                    if (xon) {
-                        xt = clampd(xt - alpha * p, l, u);
-                        g = g - alpha * hp;
-                        const Split f = split(xt, g, l, u, abar);
-                        if (kind == STEP_EXPAND) {
-                            xt = clampd(xt - abar * f.phi, l, u);
-                            sxt[tid] = xt;
-                        } else {
-                            us[0] = f.phi * f.phi + f.beta * f.beta;
-                            us[1] = f.beta * f.beta;
-                            us[2] = f.phit * f.phi;
-                            us[3] = f.phi * hp;
-                        }
-                    }
-                    ++inner;
-                    if (kind == STEP_EXPAND) {
-                        __syncthreads();
-                        const double qx = qdot(sxt);
-                        if (xon) {
-                            g = qx + it * xt - rhs;
-                            const Split f = split(xt, g, l, u, abar);
-                            us[0] = f.phi * f.phi + f.beta * f.beta;
-                            us[1] = f.beta * f.beta;
-                            us[2] = f.phit * f.phi;
-                        }
-                    }
-                    step_sum<false>(us, redu);
-                    if (kind == STEP_CG) gam = uniform(us[3] / hs[0]);
-                    done = uniform_int(sqrt(us[0]) <= eps_use || inner >= P.max_inner);
-                    const bool prop = us[1] <= gamma2 * us[2];
-                    mode = uniform_int(!prop ? DIR_BETA : (kind == STEP_CG ? DIR_CONJ : DIR_PHI));
-                }
-                inner_total += inner;
+                cg.eps = P.eps_fixed > 0.0 ? P.eps_fixed : eps;
+                cg.steps = 0;
+                inner_solve(cg, Q, xon, live, l, u, rhs, xt, g, st, sp, sxt, redh, redu);
+                inner_total += cg.steps;
                 // x_bar
                 if (xon) {
                     sxt[tid] = xt;
@@ -392,7 +473,7 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
                     if (store) B.xt[vi] = xt;
                 }
                 double mv[4] = {dx * dx, dy * dy, 0.0, 0.0};
-                step_sum<false>(mv, redh);   // its barrier also publishes y
+                step_sum<false>(mv, any, redh);   // its barrier also publishes y
                 if (P.eps_fixed <= 0.0)
                     eps = uniform(fmin(eps, fmax(P.gamma_inner * omega * sqrt(mv[0]) / tau, P.eps_min)));
                 if (store) {   // the certificate pieces
@@ -442,6 +523,203 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
         }
         __syncthreads();
     }
+}
+
+// ---- one problem on one CU --------------------------------------------------------
+//
+// The same for a single problem: whole iterations up to the next check, as
+// coop.hip's kernel makes them with a group of workgroups (the gradient
+// updated from the previous subproblem's), whose rounds cost 5 us each: a
+// random QP with n = 1000 to its tolerance takes 80 ms here, about 140 there
+// and 363 launch by launch.
+__global__ __launch_bounds__(REG_MAX) void k_single_solve(DevState S, CoopRun R)
+{
+    __shared__ double sh[LDS_ALL];
+    double* red = sh + AT_RED;
+    double* redh = sh + AT_STEP;
+    double* redu = redh + 16 * WAVES;
+    double* sp = sh + AT_OPS;
+    double* sxt = sh + AT_OPS + OP;
+    double* sy = sh + AT_OPS + 2 * OP;
+    int* misc = reinterpret_cast<int*>(sh + AT_MISC);
+    unsigned short* place = reinterpret_cast<unsigned short*>(sh + AT_DEAL);
+    unsigned short* var = place + REG_MAX;
+    double* lqv = sh + AT_REST;
+    unsigned short* lqo = reinterpret_cast<unsigned short*>(lqv + REST_Q);
+    double* lav = sh + AT_A;
+    unsigned short* lao = reinterpret_cast<unsigned short*>(lav + A_PLACES);
+    const int tid = threadIdx.x, n = S.n, m = S.m;
+    const bool xon = tid < n, yon = tid < m;
+    const bool live = uniform_int(tid & ~63) < n, any = uniform_int(tid & ~63) < (n > m ? n : m);
+    deal_rows(n, S.Q.rowptr, reinterpret_cast<int*>(sh + AT_OPS), place, var);
+    const int vi = xon ? (int)var[tid] : 0, ri = yon ? tid : 0;
+    const int qa = xon ? S.Q.rowptr[vi] : 0, ql = xon ? S.Q.rowptr[vi + 1] - qa : 0;
+    const int ta = xon ? S.AT.rowptr[vi] : 0, tl = xon ? S.AT.rowptr[vi + 1] - ta : 0;
+    const int aa = yon ? S.A.rowptr[ri] : 0, al = yon ? S.A.rowptr[ri + 1] - aa : 0;
+    const int qmost = longest(ql), amost = longest(al);
+    const Share qs = share(qmost > REG_Q ? qmost - REG_Q : 0, REST_Q, misc + 16);
+    const Share as = share(amost, A_PLACES, misc + 16);
+    fill(qs, qa, ql, REG_Q, S.Q.val, nullptr, S.Q.col, 0, place, n, lqv, lqo);
+    fill(as, aa, al, 0, S.A.val, nullptr, S.A.col, 0, place, n, lav, lao);
+    RowQ Q;
+    Q.most = qmost;
+    Q.base = qs.base;
+    Q.wide = qs.wide;
+    Q.lv = lqv;
+    Q.lo = lqo;
+    Q.load(qa, ql, S.Q.val, nullptr, S.Q.col, 0, place, n);
+    for (int i = tid; i < 3 * OP; i += REG_MAX) sh[AT_OPS + i] = 0.0;
+    __syncthreads();
+
+    const Ctrl* c0 = S.ctrl;
+    const double tau = uniform(c0->tau), sigma = uniform(c0->sigma), omega = uniform(c0->omega), th = uniform(c0->theta);
+    const double gamma_inner = uniform(c0->gamma_inner), eps_min = uniform(c0->eps_min), eps_fixed = uniform(c0->eps_fixed);
+    const int halpern = uniform_int(c0->use_halpern), unb = uniform_int(c0->has_unbounded_x);
+    const double it = uniform(c0->inv_tau);
+    Inner cg;
+    cg.it = it;
+    cg.abar = uniform(c0->abar);
+    cg.gamma2 = uniform(c0->mprgp_gamma) * uniform(c0->mprgp_gamma);
+    cg.max_inner = c0->max_inner;
+    double eps = uniform(c0->eps), g_it = uniform(c0->g_inv_tau), ndx2 = uniform(c0->ndx2), ndy2 = uniform(c0->ndy2);
+    double R_start = uniform(c0->R_start), res = 0.0;
+    double cert[5] = {uniform(c0->ytil_max), uniform(c0->ptil_sum), uniform(c0->ptil_abs), uniform(c0->d_max), uniform(c0->cd)};
+    long long inner_total = 0;
+
+    const double l = xon ? S.lv[vi] : -INFINITY, u = xon ? S.uv[vi] : INFINITY;
+    double x = xon ? S.x[vi] : 0.0, y = yon ? S.y[ri] : 0.0, xt = xon ? S.xt[vi] : 0.0;
+    double rhs = xon ? S.rhs[vi] : 0.0, g = xon ? S.g[vi] : 0.0, yt = 0.0;
+    if (xon) sxt[tid] = xt;
+    if (yon) sy[tid] = y;
+    __syncthreads();
+
+    for (int iter = 0; iter < R.iters; ++iter) {
+        const long long k = R.k + iter, t = R.t + iter;
+        const bool store = !R.sub && (((k + 1) % R.check_every == 0) || (k + 1 >= R.max_iter));
+        const bool exact = R.exact && iter == 0;
+        // right-hand side and the gradient at the warm start
+        double st[4] = {0.0, 0.0, 0.0, 0.0};
+        if (live) {
+            double r = rhs;
+            if (!R.sub) {
+                double aty = 0.0;
+#pragma unroll 4
+                for (int q = 0; q < tl; ++q) aty += S.AT.val[ta + q] * sy[S.AT.col[ta + q]];
+                if (xon) r = x * it - S.c[vi] - aty;
+            }
+            double qx = 0.0;
+            if (exact) qx = Q.dot(sxt);
+            if (xon) {
+                g = exact ? qx + it * xt - r : g + (rhs - r) + xt * (it - g_it);
+                rhs = r;
+                const Split f = split(xt, g, l, u, cg.abar);
+                st[0] = f.phi * f.phi + f.beta * f.beta;
+                st[1] = f.beta * f.beta;
+                st[2] = f.phit * f.phi;
+            }
+        }
+        step_sum<false>(st, live, redu);
+        if (exact && isinf(eps) && eps_fixed <= 0.0) eps = uniform(fmax(gamma_inner * sqrt(st[0]), eps_min));
+        g_it = it;
+        cg.eps = eps_fixed > 0.0 ? eps_fixed : eps;
+        cg.steps = 0;
+        inner_solve(cg, Q, xon, live, l, u, rhs, xt, g, st, sp, sxt, redh, redu);
+        inner_total += cg.steps;
+        res = sqrt(st[0]);
+        if (R.sub) break;
+        // x_bar
+        if (xon) {
+            sxt[tid] = xt;
+            sp[tid] = 2.0 * xt - x;
+        }
+        __syncthreads();
+        // dual step and the Halpern averages of y and x
+        const double tt = (double)t, w = (tt + 1.0) / (tt + 2.0), wa = 1.0 / (tt + 2.0);
+        double dy = 0.0, dx = 0.0, lc = 0.0, uc = 0.0;
+        if (amost > 0 || yon) {
+            const int f = as.base + (tid & 63);
+            double ax = 0.0;
+#pragma unroll 4
+            for (int q = 0; q < as.wide; ++q) ax += lav[f + 64 * q] * sp[lao[f + 64 * q]];
+            for (int q = as.wide; q < al; ++q) ax += S.A.val[aa + q] * sp[place[S.A.col[aa + q]]];
+            if (yon) {
+                lc = S.lc[ri];
+                uc = S.uc[ri];
+                const double v = y / sigma + ax;
+                yt = sigma * (v - clampd(v, lc, uc));
+                dy = yt - y;
+                y = halpern ? w * ((1.0 + th) * yt - th * y) + wa * S.ya[ri] : yt;
+                sy[tid] = y;
+            }
+        }
+        if (xon) {
+            dx = xt - x;
+            x = halpern ? w * ((1.0 + th) * xt - th * x) + wa * S.xa[vi] : xt;
+        }
+        double mv[4] = {dx * dx, dy * dy, 0.0, 0.0};
+        step_sum<false>(mv, any, redh);   // its barrier also publishes y
+        ndx2 = mv[0];
+        ndy2 = mv[1];
+        if (eps_fixed <= 0.0) eps = uniform(fmin(eps, fmax(gamma_inner * omega * sqrt(ndx2) / tau, eps_min)));
+        if (t == 0) R_start = uniform(sqrt(omega * ndx2 + ndy2 / omega));
+        if (store) {   // the certificate pieces
+            double a[5] = {0, 0, 0, 0, 0};
+            if (yon) {
+                const double yy = projY(dy, lc, uc);
+                S.ytil[ri] = yy;
+                a[0] = fabs(yy);
+                a[1] = supp(yy, lc, uc);
+                a[2] = supp_abs(yy, lc, uc);
+            }
+            if (xon && unb) {
+                const double di = projRec(dx, l, u);
+                S.dx[vi] = di;
+                a[3] = fabs(di);
+                a[4] = S.c[vi] * di;
+            }
+            wg_sum<5, 1u | (1u << 3)>(a, red);
+#pragma unroll
+            for (int j = 0; j < 5; ++j) cert[j] = a[j];
+        }
+    }
+    if (xon) {
+        S.xt[vi] = xt;
+        S.g[vi] = g;
+        S.rhs[vi] = rhs;
+        S.x[vi] = x;
+    }
+    if (yon && !R.sub) {
+        S.y[ri] = y;
+        S.yt[ri] = yt;
+    }
+    if (tid == 0) {
+        Ctrl* c = S.ctrl;
+        c->eps = eps;
+        c->g_inv_tau = g_it;
+        c->inner_it = cg.steps;
+        c->inner_total += inner_total;
+        c->hp_active += cg.products;
+        c->res = res;
+        if (!R.sub) {
+            c->k = R.k + R.iters;
+            c->t = R.t + R.iters;
+            c->ndx2 = ndx2;
+            c->ndy2 = ndy2;
+            c->R_start = R_start;
+            c->ytil_max = cert[0];
+            c->ptil_sum = cert[1];
+            c->ptil_abs = cert[2];
+            c->d_max = cert[3];
+            c->cd = cert[4];
+        }
+        post_status(S.dstat, R.iters, 0);
+    }
+}
+
+hipError_t launch_single_solve(const DevState& S, const CoopRun& R, hipStream_t s)
+{
+    k_single_solve<<<1, REG_MAX, 0, s>>>(S, R);
+    return hipGetLastError();
 }
 
 hipError_t launch_general_solve(const BatchDev& B, const BatchParams& P, hipStream_t s)

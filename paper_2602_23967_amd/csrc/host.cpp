@@ -48,6 +48,7 @@ struct qp_handle {
     int qkind = 0;   // 0 none, 1 diagonal, 2 general
     double setup_seconds = 0.0;
     CoopDev coop;    // coop.ns > 0: solves run in the kernel of coop.hip
+    int single = 0;  // they run in the kernel of general.hip
     // timing
     std::vector<EventPair> ev_pool;
     size_t ev_used = 0;
@@ -248,13 +249,34 @@ int64_t longest_row(int64_t rows, const int64_t* rp)
     return l;
 }
 
-// prepares the one-launch iteration where the problem fits it (coop.ns > 0)
+// A Q with n rows at rp whose rows the kernels of general.hip hold: dealt by
+// length to waves of 64 rows, what is past the registers has a place in LDS.
+// (A row read from memory in every step is what the general kernels do, with
+// more workgroups or threads.)
+bool one_cu_fits(int64_t n, int64_t m, const int64_t* rp)
+{
+    if (n < 1 || n > ONE_CU_MAX || m > ONE_CU_MAX) return false;
+    std::vector<int64_t> len(n);
+    for (int64_t i = 0; i < n; ++i) len[i] = rp[i + 1] - rp[i];
+    std::sort(len.begin(), len.end(), [](int64_t a, int64_t b) { return a > b; });
+    int64_t places = 0;
+    for (int64_t i = 0; i < n; i += 64) places += 64 * std::max<int64_t>(0, len[i] - ONE_CU_REG_Q);
+    return places <= ONE_CU_REST_Q;
+}
+
+// prepares the one-launch iteration where the problem fits it (single, or coop.ns > 0)
 int coop_create(qp_handle* h, const int64_t* qp, const int64_t* ap, const int64_t* tp)
 {
     const DevState& S = h->S;
     const int64_t n = h->n, m = h->m;
     if (h->qkind != 2 || S.k > 0 || S.Q.nparts > 1 || S.A.nparts > 1 || S.AT.nparts > 1) return 0;
     if (longest_row(n, qp) > COOP_ROW || longest_row(m, ap) > COOP_ROW || longest_row(n, tp) > COOP_COL) return 0;
+    if (one_cu_fits(n, m, qp)) {
+        // (n = 1000 to its tolerance: 363 ms launch by launch, about 140
+        // with a group of workgroups, 80 on one CU)
+        h->single = 1;
+        return 0;
+    }
     int dev = 0, cus = 0;
     HIPCHK(hipGetDevice(&dev));
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -289,11 +311,11 @@ int coop_create(qp_handle* h, const int64_t* qp, const int64_t* ap, const int64_
     return 0;
 }
 
-// one launch of coop.hip's kernel; `done`: the iterations it made
+// one launch of coop.hip's or general.hip's kernel; `done`: the iterations it made
 int coop_run(qp_handle* h, const CoopRun& R, int* done)
 {
     h->hstat[0] = 0;
-    HIPCHK(launch_coop(h->S, h->coop, R, h->stream));
+    HIPCHK(h->single ? launch_single_solve(h->S, R, h->stream) : launch_coop(h->S, h->coop, R, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     const unsigned long long w = *(volatile unsigned long long*)h->hstat;
     *done = (int)(w >> 1);
@@ -847,7 +869,7 @@ int qp_solve_ex(qp_handle* h, const qp_params* params)
     const double t0 = now_s();
     if (int rc = set_precision(h, p.precision)) return rc;
     // inner steps per graph launch (eager launches when timing kernel families)
-    const bool coop = h->coop.ns > 0 && p.timing == 0 && p.max_inner <= COOP_INNER && p.precision == QP_PRECISION_FP64;
+    const bool coop = (h->single || h->coop.ns > 0) && p.timing == 0 && p.max_inner <= COOP_INNER && p.precision == QP_PRECISION_FP64;
     const int K = (p.timing > 0 || S.qdiag || coop) ? 0 : p.graph_steps;
     if (K > 0)
         if (int rc = ensure_inner_graph(h, K)) return rc;
@@ -1090,7 +1112,7 @@ int qp_subproblem(qp_handle* h, double tau, const double* rhs, double* x, double
     HIPCHK(launch_clip(S, S.xt, s));
     HIPCHK(hipStreamSynchronize(s));
     int rc = 0;
-    if (h->coop.ns > 0 && max_inner <= COOP_INNER) {
+    if ((h->single || h->coop.ns > 0) && max_inner <= COOP_INNER) {
         CoopRun R;
         R.iters = R.exact = R.sub = 1;
         int done = 0;
@@ -1419,6 +1441,10 @@ int batch_create(hipStream_t lane, int64_t count, const int64_t* var_off, const 
             return var_off[i + 1] - var_off[i] <= ONE_CU_MAX && row_off[i + 1] - row_off[i] <= ONE_CU_MAX;
         };
         auto closed = [&](int i) { return !qgen[i] && one_cu(i); };
+        std::vector<char> fits(count, 0);
+        for (int64_t i = 0; i < count; ++i)
+            fits[i] = qgen[i] && one_cu_fits(var_off[i + 1] - var_off[i], row_off[i + 1] - row_off[i], Qp + var_off[i]);
+        auto general = [&](int i) { return fits[i] != 0; };
         std::vector<int> lists(perm);   // dorder, then the two split orders
         for (int64_t i = 0; i < count; ++i) lists.push_back((int)i);
         lists.insert(lists.end(), perm.begin(), perm.end());
@@ -1426,7 +1452,7 @@ int batch_create(hipStream_t lane, int64_t count, const int64_t* var_off, const 
             const auto first = lists.begin() + o * count, end = first + count;
             const auto second = std::stable_partition(first, end, closed);
             bt->nclosed = (int)(second - first);
-            bt->ngeneral = (int)(std::stable_partition(second, end, one_cu) - second);
+            bt->ngeneral = (int)(std::stable_partition(second, end, general) - second);
         }
         // (a batch in the static workspace keeps its schedule: one list, so
         // the same batches fit as with a plain order)

@@ -221,6 +221,8 @@ struct CoopRun {
     int exact = 0;                     // the first gradient is formed with a product with Q
     int sub = 0;                       // one subproblem only: rhs given, no outer step
 };
+// the same on one CU (general.hip), for problems that one_cu_fits (host.cpp)
+hipError_t launch_single_solve(const DevState& S, const CoopRun& R, hipStream_t s);
 // posts the iterations done in the status word (flag set: a wait gave up)
 hipError_t launch_coop(const DevState& S, const CoopDev& D, const CoopRun& R, hipStream_t s);
 
@@ -308,6 +310,8 @@ hipError_t launch_batch_solve(const BatchDev& B, const BatchParams& P, int shape
 // general_list (general.hip): inner solves; at most ONE_CU_MAX variables and
 // rows each
 constexpr int ONE_CU_MAX = 1024;
+constexpr int ONE_CU_REG_Q = 16;     // entries of a row of Q in registers
+constexpr int ONE_CU_REST_Q = 5632;  // LDS places for the others (64 rows of a wave as long as the longest)
 hipError_t launch_closed_solve(const BatchDev& B, const BatchParams& P, hipStream_t s);
 hipError_t launch_general_solve(const BatchDev& B, const BatchParams& P, hipStream_t s);
 hipError_t launch_closed_norm(const BatchDev& B, double tol, long long max_iter, double* out, hipStream_t s);

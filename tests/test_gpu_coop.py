@@ -51,11 +51,12 @@ def _qp(n, m, qrow=4, acol=0, seed=0, unbounded=False):
                 lb=lb, ub=ub, name=f"coop_{n}_{m}")
 
 
-# slices: one, its row limit (256) met and passed, its entry limit, several, more rows of A than of Q;
+# on one CU: up to 1000 variables; with a group of workgroups: the longest
+# rows, more than 1024 variables or rows.  Its row limit (256) met and passed, more rows of A than of Q;
 # the longest row and column that the path takes, and one entry more (then both routes are one)
 CASES = [dict(n=1, m=1), dict(n=3, m=0), dict(n=255, m=128), dict(n=256, m=300), dict(n=257, m=64),
          dict(n=700, m=2000), dict(n=1000, m=500, qrow=255), dict(n=1000, m=500, qrow=256),
-         dict(n=600, m=400, acol=64), dict(n=600, m=400, acol=65), dict(n=5000, m=2500, unbounded=True),
+         dict(n=1024, m=1024), dict(n=1025, m=3), dict(n=600, m=400, acol=64), dict(n=600, m=400, acol=65), dict(n=5000, m=2500, unbounded=True),
          dict(n=40000, m=9000)]
 
 
