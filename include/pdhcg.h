@@ -91,7 +91,8 @@ typedef struct {
     int graph_steps;          /* > 0: the inner solve's steps are launched as a captured HIP
                                  graph of this many steps (0: one launch per kernel; timing
                                  forces 0); results are the same either way; 0 (measured
-                                 slower: the steps are bound by the GPU, not by launches) */
+                                 slower: the steps are bound by the GPU, not by launches);
+                                 no effect where whole iterations run in one launch */
     int reserved;
 } qp_params;
 
