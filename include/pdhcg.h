@@ -338,9 +338,10 @@ int qp_batch_solve_static(int64_t count, const int64_t* var_off, const int64_t* 
  * the instance sizes, hence the tuner.  The order never changes a result;
  * the shape may change the last bits (a workgroup reduction groups its
  * terms by the workgroup size), and each shape is deterministic.  Under the
- * default shape an instance with a diagonal Q and at most 1024 variables and
- * rows gets a whole CU, four such workgroups in one of 1024 threads, which
- * holds its matrices in registers and LDS. */
+ * two default shapes an instance with at most 1024 variables and rows gets a
+ * whole CU and a workgroup of 1024 threads, which holds its matrices in
+ * registers and LDS; with a non-diagonal Q in FP64 only, and if the CU holds
+ * its rows of Q. */
 
 /* Number of compiled shapes, and shape i's threads per workgroup, LDS
  * doubles and the waves per SIMD its register allocation leaves room for
