@@ -282,8 +282,8 @@ int coop_create(qp_handle* h, const int64_t* qp, const int64_t* ap, const int64_
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     // Slices of 256 rows up to 128 of them, then of 512: every workgroup reads
     // every slice's words in a round (random QPs, 128 iterations, slices of
-    // 256 and of 512: n = 3000 13.2 and 17.0 ms, n = 20,011 23.4 and 24.1 ms
-    // with 108 and 54 slices, n = 50,000 56.3 and 38.5 ms with 270 and 135).
+    // 256 and of 512: n = 3000 13.2 and 17.0 ms, n = 8000 16.0 and 18.6, n =
+    // 20,011, just past the line, 23.4 and 24.1, n = 50,000 56.3 and 38.5).
     int threads = 256;
     std::vector<BlkDesc> q = coop_slices(n, qp, threads);
     if ((int)q.size() > 128) q = coop_slices(n, qp, threads = 512);
