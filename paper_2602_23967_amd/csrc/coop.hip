@@ -23,8 +23,9 @@
 // and the round's number, so one load both waits for a value and reads it.
 // No cache is flushed or invalidated.
 //
-// Progress.  The rows are cut into slices that do not depend on the device;
-// workgroup i of W takes slices i, i + W, ...  W is how many workgroups had
+// Progress.  The rows are cut into slices that do not depend on W; workgroup i
+// of W takes slices i, i + W, ..., at least one of each matrix, so that it
+// posts in every round (coop_rounds.h: why it has to).  W is how many workgroups had
 // started when the first of them closed the list (all of the grid, or those
 // that came within REG_WAIT_US): nobody waits for a workgroup that has not
 // started, so kernels of other streams cannot block the group, and the
@@ -35,6 +36,7 @@
 // bit can turn the FP32 rounding of an operand, and results moved by 1e-8.
 #include <math.h>
 
+#include "coop_rounds.h"
 #include "device_math.h"
 #include "pdhcg_internal.h"
 
@@ -103,7 +105,7 @@ struct Group {
             for (int w = 1; w < T / 64; ++w) r = rcomb(kind_of(KINDS, j), r, red[4 * w + j]);
             const u64 b = (u64)__double_as_longlong(r);
             const u64 half = (threadIdx.x & 1) ? b >> 32 : b & 0xffffffffull;
-            agent_store(&slots[(size_t)8 * s + threadIdx.x], ((u64)tag << 32) | half);
+            agent_store(&slots[coop_slot(0, 0, s) + threadIdx.x], ((u64)tag << 32) | half);
         }
         __syncthreads();
     }
@@ -238,7 +240,7 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
             av[i] = in ? S.Q.val[qb.k0 + q] : 0.0;
         }
     };
-    if (one && G.me < NS) enter(G.me);   // rows of A alone can make more workgroups than Q has slices
+    if (one) enter(G.me);   // (there are NS >= W slices)
 
     // row of Q times an operand: the block's products in LDS, the thread's row
     // summed in its order; xop(j): FP64 operand
@@ -256,7 +258,7 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
         __syncthreads();
         return s;
     };
-    auto qslots = [&]() { return D.slots + (size_t)(G.tag & 1) * 8 * NS; };
+    auto slots = [&]() { return D.slots + coop_slot(G.tag, D.nslots, 0); };   // of the next round
 
     for (int iter = 0; iter < iters; ++iter) {
         const long long k = R.k + iter, t = R.t + iter;
@@ -292,9 +294,9 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
                 a[2] = sp.phit * sp.phi;
                 peer_store(&e0[i], sp.phi);
             }
-            G.template post<kinds4(0, 0, 0, 0)>(qslots(), s, a);
+            G.template post<kinds4(0, 0, 0, 0)>(slots(), s, a);
         }
-        G.template wait<kinds4(0, 0, 0, 0)>(qslots(), NS, v);
+        G.template wait<kinds4(0, 0, 0, 0)>(slots(), NS, v);
         if (exact && isinf(eps) && eps_fixed <= 0.0) eps = uniform(fmax(gamma_inner * sqrt(v[0]), eps_min));
         g_it = it;
         inner_it = 0;
@@ -311,9 +313,9 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
                     if (!one) enter(s);
                     double a[4] = {0.0, 0.0, 0.0, 0.0};
                     if (own) peer_store(&e0[row], split(S.xt[row], S.g[row], S.lv[row], S.uv[row], abar).beta);
-                    G.template post<kinds4(0, 0, 0, 0)>(qslots(), s, a);
+                    G.template post<kinds4(0, 0, 0, 0)>(slots(), s, a);
                 }
-                G.template wait<kinds4(0, 0, 0, 0)>(qslots(), NS, v);
+                G.template wait<kinds4(0, 0, 0, 0)>(slots(), NS, v);
             }
             // H p = Q p + p / tau with p'Hp, g'p and the feasible step
             const int conj = mode == DIR_CONJ;
@@ -339,9 +341,9 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
                     if (p > 0.0 && isfinite(l)) a[3] = (xi - l) / p;
                     else if (p < 0.0 && isfinite(u)) a[3] = (xi - u) / p;
                 }
-                G.template post<kinds4(0, 0, 0, 2)>(qslots(), s, a);
+                G.template post<kinds4(0, 0, 0, 2)>(slots(), s, a);
             }
-            G.template wait<kinds4(0, 0, 0, 2)>(qslots(), NS, v);
+            G.template wait<kinds4(0, 0, 0, 2)>(slots(), NS, v);
             if (uniform_int(!(v[0] > 0.0))) break;   // no descent direction left
             const double pHp = v[0], af = v[3] < 0.0 ? 0.0 : v[3], acg = v[1] / v[0];
             int kind;
@@ -375,9 +377,9 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
                     }
                     S.xt[i] = xi;
                 }
-                G.template post<kinds4(0, 0, 0, 0)>(qslots(), s, a);
+                G.template post<kinds4(0, 0, 0, 0)>(slots(), s, a);
             }
-            G.template wait<kinds4(0, 0, 0, 0)>(qslots(), NS, v);
+            G.template wait<kinds4(0, 0, 0, 0)>(slots(), NS, v);
             ++inner_it;
             ++inner_total;
             if (kind == STEP_EXPAND) {
@@ -397,9 +399,9 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
                         a[2] = sp.phit * sp.phi;
                         peer_store(&e0[i], sp.phi);
                     }
-                    G.template post<kinds4(0, 0, 0, 0)>(qslots(), s, a);
+                    G.template post<kinds4(0, 0, 0, 0)>(slots(), s, a);
                 }
-                G.template wait<kinds4(0, 0, 0, 0)>(qslots(), NS, v);
+                G.template wait<kinds4(0, 0, 0, 0)>(slots(), NS, v);
             } else if (kind == STEP_CG) {
                 gam = uniform(v[3] / pHp);
             }
@@ -430,9 +432,9 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
                     a[2] = S.c[i] * di;
                 }
             }
-            G.template post<kinds4(0, 1, 0, 0)>(qslots(), s, a);
+            G.template post<kinds4(0, 1, 0, 0)>(slots(), s, a);
         }
-        G.template wait<kinds4(0, 1, 0, 0)>(qslots(), NS, v);
+        G.template wait<kinds4(0, 1, 0, 0)>(slots(), NS, v);
         ndx2 = v[0];
         if (store) {
             d_max = unb ? v[1] : 0.0;
@@ -441,8 +443,6 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
         if (eps_fixed <= 0.0) eps = uniform(fmin(eps, fmax(gamma_inner * omega * sqrt(ndx2) / tau, eps_min)));
 
         // ---- dual step and the Halpern average of y --------------------------------------
-        const unsigned par = (unsigned)iter & 1u;
-        u64* const as = D.aslots + (size_t)par * 8 * NSA;
         for (int s = G.me; s < NSA; s += G.W) {
             const BlkDesc ab = D.ablk[s];
             const int cnt = ab.k1 - ab.k0;
@@ -485,9 +485,9 @@ __global__ __launch_bounds__(T) void k_coop(DevState S, CoopDev D, CoopRun R)
                     a[3] = supp_abs(yy, l, u);
                 }
             }
-            G.template post<kinds4(0, 1, 0, 0)>(as, s, a);
+            G.template post<kinds4(0, 1, 0, 0)>(slots(), s, a);
         }
-        G.template wait<kinds4(0, 1, 0, 0)>(as, NSA, v);
+        G.template wait<kinds4(0, 1, 0, 0)>(slots(), NSA, v);
         ndy2 = v[0];
         if (store) {
             ytil_max = v[1];
@@ -533,7 +533,7 @@ __global__ __launch_bounds__(256) void k_coop_begin(CoopDev D, long long words)
 
 hipError_t launch_coop(const DevState& S, const CoopDev& D, const CoopRun& R, hipStream_t s)
 {
-    const long long words = 16ll * (D.ns + D.nsa);   // both parities of both slot arrays (one allocation)
+    const long long words = 16ll * D.nslots;
     k_coop_begin<<<(int)((words + 255) / 256), 256, 0, s>>>(D, words);
     const int grid = D.full;
     if (D.threads == 256) k_coop<256><<<grid, 256, 0, s>>>(S, D, R);

@@ -229,19 +229,6 @@ int upload_csr(qp_handle* h, CsrDev& M, int64_t rows, int64_t cols, const int64_
     return 0;
 }
 
-// Slices of a CSR for coop.hip: whole rows, at most `threads` of them with at
-// most COOP_EPT entries per thread.
-std::vector<BlkDesc> coop_slices(int64_t rows, const int64_t* rp, int threads)
-{
-    std::vector<BlkDesc> s;
-    for (int64_t r = 0; r < rows;) {
-        const int64_t a = r;
-        while (r < rows && r - a < threads && rp[r + 1] - rp[a] <= (int64_t)COOP_EPT * threads) ++r;
-        s.push_back({(int)a, (int)(r - a), (int)rp[a], (int)rp[r], 0, 0, 0, 0});
-    }
-    return s;
-}
-
 int64_t longest_row(int64_t rows, const int64_t* rp)
 {
     int64_t l = 0;
@@ -280,33 +267,23 @@ int coop_create(qp_handle* h, const int64_t* qp, const int64_t* ap, const int64_
     int dev = 0, cus = 0;
     HIPCHK(hipGetDevice(&dev));
     HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    // Slices of 256 rows up to 128 of them, then of 512: every workgroup reads
-    // every slice's words in a round (random QPs, 128 iterations, slices of
-    // 256 and of 512: n = 3000 13.2 and 17.0 ms, n = 8000 16.0 and 18.6, n =
-    // 20,011, just past the line, 23.4 and 24.1, n = 50,000 56.3 and 38.5).
-    int threads = 256;
-    std::vector<BlkDesc> q = coop_slices(n, qp, threads);
-    if ((int)q.size() > 128) q = coop_slices(n, qp, threads = 512);
-    // At most one slice per compute unit, whose entries then stay in
-    // registers: at n = 50,000 a solve took 80.6 ms launch by launch and takes
-    // 38.5, but at n = 200,003 (391 slices) an inner solve took 2.16 and 2.22.
-    if ((int)q.size() > cus) return 0;
-    const std::vector<BlkDesc> a = coop_slices(m, ap, threads);
+    CoopLayout L;
+    if (!coop_layout(n, qp, m, ap, cus, L)) return 0;
     CoopDev D;
-    D.ns = (int)q.size();
-    D.nsa = (int)a.size();
-    D.full = std::min(std::max(D.ns, D.nsa), cus);
-    D.threads = threads;
+    D.ns = (int)L.q.size();
+    D.nsa = (int)L.a.size();
+    D.nslots = std::max(D.ns, D.nsa);
+    D.full = L.full;
+    D.threads = L.threads;
     BlkDesc *dq, *da;
     int rc;
-    if ((rc = upload(h, &dq, q.data(), q.size())) || (rc = upload(h, &da, a.data(), a.size())) ||
+    if ((rc = upload(h, &dq, L.q.data(), L.q.size())) || (rc = upload(h, &da, L.a.data(), L.a.size())) ||
         (rc = dalloc(h, &D.ex, (size_t)2 * n)) ||
-        (rc = dalloc(h, &D.ey, (size_t)m)) || (rc = dalloc(h, &D.slots, (size_t)16 * (D.ns + D.nsa))) ||
+        (rc = dalloc(h, &D.ey, (size_t)m)) || (rc = dalloc(h, &D.slots, (size_t)16 * D.nslots)) ||
         (rc = dalloc(h, &D.reg, 4)))
         return rc;
     D.qblk = dq;
     D.ablk = da;
-    D.aslots = D.slots + (size_t)16 * D.ns;
     h->coop = D;
     return 0;
 }

@@ -201,17 +201,17 @@ int vec_grid(long long len);
 
 // ---- one problem's iterations in one launch (coop.hip) -------------------------
 
-constexpr int COOP_EPT = 8;          // matrix entries per thread and slice at most
 constexpr int COOP_ROW = 256;        // entries of a row of Q and A at most (one thread sums it)
 constexpr int COOP_COL = 64;         // entries of a column of A at most
 constexpr int COOP_ITERS = 256;      // iterations of a launch at most
 constexpr int COOP_INNER = 100000;   // inner steps per iteration at most (bounds a launch's time)
 struct CoopDev {
     int ns = 0, nsa = 0;               // slices of the variables (rows of Q) and of the rows of A
-    int full = 0, threads = 0;         // workgroups of a launch, threads of each
+    int nslots = 0;                    // slots of a round's set: the more of these
+    int full = 0, threads = 0;         // workgroups of a launch (each has a slice of both), threads of each
     const BlkDesc *qblk = nullptr, *ablk = nullptr;   // the slices: rows and entries (whole rows)
     double *ex = nullptr, *ey = nullptr;              // exchange: two doubles per variable, one per row
-    unsigned long long *slots = nullptr, *aslots = nullptr;   // 2 x 8 words per slice; aslots follow slots
+    unsigned long long* slots = nullptr;              // two sets of nslots slots of 8 words
     int* reg = nullptr;                // workgroups started, workgroups taking part
 };
 struct CoopRun {

@@ -273,4 +273,39 @@ int classify_bounds(const std::vector<double>& lv, const std::vector<double>& uv
     return keys.size() == 1 ? 1 : 2;
 }
 
+// ---- slices of a problem whose iterations run in one launch --------------------
+
+std::vector<BlkDesc> coop_slices(int64_t rows, const int64_t* rp, int threads)
+{
+    std::vector<BlkDesc> s;
+    for (int64_t r = 0; r < rows;) {
+        const int64_t a = r;
+        while (r < rows && r - a < threads && rp[r + 1] - rp[a] <= (int64_t)COOP_EPT * threads) ++r;
+        s.push_back({(int)a, (int)(r - a), (int)rp[a], (int)rp[r], 0, 0, 0, 0});
+    }
+    return s;
+}
+
+bool coop_layout(int64_t n, const int64_t* qp, int64_t m, const int64_t* ap, int cus, CoopLayout& L)
+{
+    // Slices of 256 rows up to 128 of them, then of 512: every workgroup reads
+    // every slice's words in a round (random QPs, 128 iterations, slices of
+    // 256 and of 512: n = 3000 13.2 and 17.0 ms, n = 8000 16.0 and 18.6, n =
+    // 20,011, just past the line, 23.4 and 24.1, n = 50,000 56.3 and 38.5).
+    L.threads = 256;
+    L.q = coop_slices(n, qp, L.threads);
+    if ((int)L.q.size() > 128) L.q = coop_slices(n, qp, L.threads = 512);
+    // At most one slice per compute unit, whose entries then stay in
+    // registers: at n = 50,000 a solve took 80.6 ms launch by launch and takes
+    // 38.5, but at n = 200,003 (391 slices) an inner solve took 2.16 and 2.22.
+    if ((int)L.q.size() > cus) return false;
+    L.a = coop_slices(m, ap, L.threads);
+    const size_t most = L.q.size() > L.a.size() ? L.q.size() : L.a.size();
+    L.full = (int)(most < (size_t)cus ? most : (size_t)cus);
+    // every workgroup has a slice of both, if an empty one
+    L.q.resize((size_t)L.full, BlkDesc{0, 0, 0, 0, 0, 0, 0, 0});
+    if (L.a.size() < (size_t)L.full) L.a.resize((size_t)L.full, BlkDesc{0, 0, 0, 0, 0, 0, 0, 0});
+    return true;
+}
+
 }  // namespace pdhcg

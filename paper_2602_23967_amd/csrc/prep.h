@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/pdhcg.h"
+#include "coop_rounds.h"
 #include "schedule.h"
 
 namespace pdhcg {
