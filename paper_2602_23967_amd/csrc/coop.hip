@@ -535,7 +535,7 @@ hipError_t launch_coop(const DevState& S, const CoopDev& D, const CoopRun& R, hi
 {
     const long long words = 16ll * D.nslots;
     k_coop_begin<<<(int)((words + 255) / 256), 256, 0, s>>>(D, words);
-    const int grid = D.full;
+    const int grid = D.cap > 0 && D.cap < D.full ? D.cap : D.full;
     if (D.threads == 256) k_coop<256><<<grid, 256, 0, s>>>(S, D, R);
     else k_coop<512><<<grid, 512, 0, s>>>(S, D, R);
     return hipGetLastError();

@@ -1109,6 +1109,13 @@ int qp_subproblem(qp_handle* h, double tau, const double* rhs, double* x, double
     return 0;
 }
 
+int qp_internal_group(qp_handle* h, int32_t cap)
+{
+    if (!h || cap < 0) return fail(QP_ERR_INVALID_ARG, "bad argument");
+    h->coop.cap = cap;
+    return h->coop.full;
+}
+
 int qp_kkt(qp_handle* h, const double* x, const double* y, double* out)
 {
     if (!h || !x || (!y && h->m > 0) || !out) return fail(QP_ERR_INVALID_ARG, "NULL argument");

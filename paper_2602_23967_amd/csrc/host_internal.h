@@ -44,3 +44,9 @@ void batch_info(const qp_batch* bt, int64_t i, qp_info* info);
 int batch_results_all(qp_batch* bt, std::vector<double>& x, std::vector<double>& y);
 
 }  // namespace pdhcg
+
+// How many workgroups a solve of this handle runs as one group (coop.hip), 0
+// where it takes another path; and at most `cap` of them from now on (0: all).
+// With fewer, each has several slices, as when other streams hold the CUs; the
+// result is the same.  Not in the header: for the tests of that path.
+extern "C" int qp_internal_group(qp_handle* h, int32_t cap);

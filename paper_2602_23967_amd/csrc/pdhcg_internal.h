@@ -209,6 +209,7 @@ struct CoopDev {
     int ns = 0, nsa = 0;               // slices of the variables (rows of Q) and of the rows of A
     int nslots = 0;                    // slots of a round's set: the more of these
     int full = 0, threads = 0;         // workgroups of a launch (each has a slice of both), threads of each
+    int cap = 0;                       // > 0: at most so many start (qp_internal_group)
     const BlkDesc *qblk = nullptr, *ablk = nullptr;   // the slices: rows and entries (whole rows)
     double *ex = nullptr, *ey = nullptr;              // exchange: two doubles per variable, one per row
     unsigned long long* slots = nullptr;              // two sets of nslots slots of 8 words

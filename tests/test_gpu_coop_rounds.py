@@ -23,7 +23,7 @@ def torch():
     return T
 
 
-SHAPES = [(3000, 0), (3000, 1), (1025, 0), (1100, 9000), (1500, 4000), (1100, 70000)]
+SHAPES = [(3000, 0), (3000, 1), (1025, 0), (1100, 9000), (1500, 4000), (10000, 70000)]
 
 
 @pytest.mark.parametrize("n, m", SHAPES)
