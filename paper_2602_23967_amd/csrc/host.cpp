@@ -12,14 +12,13 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
-#include <mutex>
-#include <new>
 #include <string>
 #include <vector>
 
 #include "../../include/pdhcg.h"
 #include "host_internal.h"
 #include "pdhcg_internal.h"
+#include "read_ahead.h"
 
 using namespace pdhcg;
 
@@ -1164,15 +1163,8 @@ struct qp_batch {
     int nclosed = 0, ngeneral = 0;
     int solved = 0;
     double setup_seconds = 0.0, solve_seconds = 0.0;
-    // results of the last solve already on the host: instances [i0, i1)
-    struct ReadAhead {
-        std::mutex lock;
-        int64_t i0 = 0, i1 = 0, next = 1;   // next: the instance after the last one asked for
-        std::vector<double> x, y;
-    };
-    mutable ReadAhead ahead;
+    mutable ReadAhead ahead;   // results of the last solve already on the host
 };
-constexpr int64_t READ_AHEAD = 1 << 18;   // doubles in a block at most (2 MiB)
 
 namespace {
 
@@ -1549,11 +1541,7 @@ int batch_launch(qp_batch* bt, const qp_params* params)
     P.gamma_inner = p.gamma_inner; P.eps_min = p.eps_min; P.eps_fixed = p.eps_inner_fixed;
     P.mprgp_gamma = p.mprgp_gamma; P.abar_scale = p.mprgp_abar_scale; P.max_inner = p.max_inner;
     bt->t_launch = now_s();
-    {
-        std::lock_guard<std::mutex> hold(bt->ahead.lock);
-        bt->ahead.i0 = bt->ahead.i1 = 0;
-        bt->ahead.next = 1;
-    }
+    bt->ahead.drop();
     HIPCHK(hipMemsetAsync(bt->B.queue, 0, 3 * sizeof(int), bt->stream));
     // The default shapes' small instances have kernels of their own; an
     // instance's route never depends on the others in the batch.
@@ -1603,8 +1591,10 @@ void batch_info(const qp_batch* bt, int64_t i, qp_info* info)
     info->setup_seconds = bt->setup_seconds;
 }
 
-// x and y (or the certificates) of the instances [i0, i1), one copy each:
-// to x and y where not NULL
+// x and y (or the certificates) of the instances [i0, i1): to x and y where
+// not NULL.  One instance needs no host memory of its own; for more, one copy
+// of each array takes all of them (std::bad_alloc if there is no room for the
+// certificates).
 int batch_results(const qp_batch* bt, int64_t i0, int64_t i1, double* x, double* y)
 {
     const int64_t v0 = bt->voff[i0], n = bt->voff[i1] - v0, r0 = bt->roff[i0], m = bt->roff[i1] - r0;
@@ -1613,17 +1603,18 @@ int batch_results(const qp_batch* bt, int64_t i0, int64_t i1, double* x, double*
         pinf |= bt->out[i].status == QP_PRIMAL_INFEASIBLE;
         dinf |= bt->out[i].status == QP_DUAL_INFEASIBLE;
     }
-    std::vector<double> d, yl;
-    if (x && n) HIPCHK(hipMemcpyAsync(x, bt->B.xt + v0, sizeof(double) * n, hipMemcpyDeviceToHost, bt->stream));
-    if (y && m) HIPCHK(hipMemcpyAsync(y, bt->B.yt + r0, sizeof(double) * m, hipMemcpyDeviceToHost, bt->stream));
-    if (x && n && dinf) {
-        d.resize(n);
-        HIPCHK(hipMemcpyAsync(d.data(), bt->B.d + v0, sizeof(double) * n, hipMemcpyDeviceToHost, bt->stream));
-    }
-    if (y && m && pinf) {
-        yl.resize(m);
-        HIPCHK(hipMemcpyAsync(yl.data(), bt->B.ytil + r0, sizeof(double) * m, hipMemcpyDeviceToHost, bt->stream));
-    }
+    const bool one = i1 == i0 + 1;
+    std::vector<double> dv, ylv;
+    if (x && dinf && !one) dv.resize((size_t)n);
+    if (y && pinf && !one) ylv.resize((size_t)m);
+    double *d = one ? x : dv.data(), *yl = one ? y : ylv.data();
+    if (x && n && !(one && dinf))
+        HIPCHK(hipMemcpyAsync(x, bt->B.xt + v0, sizeof(double) * n, hipMemcpyDeviceToHost, bt->stream));
+    if (y && m && !(one && pinf))
+        HIPCHK(hipMemcpyAsync(y, bt->B.yt + r0, sizeof(double) * m, hipMemcpyDeviceToHost, bt->stream));
+    if (x && n && dinf) HIPCHK(hipMemcpyAsync(d, bt->B.d + v0, sizeof(double) * n, hipMemcpyDeviceToHost, bt->stream));
+    if (y && m && pinf)
+        HIPCHK(hipMemcpyAsync(yl, bt->B.ytil + r0, sizeof(double) * m, hipMemcpyDeviceToHost, bt->stream));
     HIPCHK(hipStreamSynchronize(bt->stream));
     for (int64_t i = i0; i < i1; ++i) {
         const BatchOut& o = bt->out[i];
@@ -1740,39 +1731,8 @@ int qp_batch_result(const qp_batch* bt, int64_t i, double* x, double* y, qp_info
     if (!bt || i < 0 || i >= bt->count) return fail(QP_ERR_INVALID_ARG, "bad batch or index");
     if (!bt->solved) return fail(QP_ERR_STATE, "no solve has run on this batch");
     if (x || (y && bt->roff[i + 1] > bt->roff[i])) {
-        // Instances fetched in their order come in blocks: a copy to the host
-        // takes 25 us however short it is, and two for each of 4096 MPC
-        // problems were 213 ms after a solve of 28; in blocks of READ_AHEAD
-        // doubles fetching them all is 53 ms, most of it the caller's.  Any
-        // other order copies what is asked for alone.
-        qp_batch::ReadAhead& ra = bt->ahead;
-        std::lock_guard<std::mutex> hold(ra.lock);
-        if (i < ra.i0 || i >= ra.i1) {
-            int64_t e = i + 1;
-            if (i == ra.next)
-                while (e < bt->count && bt->voff[e + 1] - bt->voff[i] + bt->roff[e + 1] - bt->roff[i] <= READ_AHEAD) ++e;
-            if (e > i + 1) {
-                ra.i0 = ra.i1 = 0;
-                try {
-                    ra.x.resize(bt->voff[e] - bt->voff[i]);
-                    ra.y.resize(bt->roff[e] - bt->roff[i]);
-                } catch (const std::bad_alloc&) {
-                    e = i + 1;   // no room on the host: this instance alone
-                }
-            }
-            if (e > i + 1) {
-                if (int rc = pdhcg::batch_results(bt, i, e, ra.x.data(), ra.y.data())) return rc;
-                ra.i0 = i;
-                ra.i1 = e;
-            } else if (int rc = pdhcg::batch_results(bt, i, e, x, y)) {
-                return rc;
-            }
-        }
-        ra.next = i + 1;
-        if (i >= ra.i0 && i < ra.i1) {
-            if (x) std::copy_n(ra.x.data() + (bt->voff[i] - bt->voff[ra.i0]), bt->voff[i + 1] - bt->voff[i], x);
-            if (y) std::copy_n(ra.y.data() + (bt->roff[i] - bt->roff[ra.i0]), bt->roff[i + 1] - bt->roff[i], y);
-        }
+        auto fetch = [bt](int64_t a, int64_t b, double* xa, double* ya) { return pdhcg::batch_results(bt, a, b, xa, ya); };
+        if (int rc = bt->ahead.get(i, bt->count, bt->voff.data(), bt->roff.data(), x, y, fetch)) return rc;
     }
     if (info) pdhcg::batch_info(bt, i, info);
     return bt->out[i].status;
