@@ -8,13 +8,22 @@
 // batched kernel (batch.hip) reads both matrices in every iteration, from the
 // memory-side cache once a batch's matrices exceed the L2s: 49 us per
 // iteration of a 748-variable MPC instance with four workgroups of 256
-// threads on a CU.  4096 MPC problems: 83 ms there, 54 here; a handful from
-// host arrays to results 28 ms and 6.  16 waves rather than 4: with one wave
-// on a SIMD the same work took twice as long, bound by instruction fetch.  The results are the general kernel's to the bit: each product sums
-// a row with one thread in row order, the norms and the weight's update take
-// their sums in its order, the Halpern averages its fused form.  (In mixed
-// precision a last bit that differs turns FP32 roundings: other orders moved
-// results by 1e-10, single entries by 3e-8.)
+// threads on a CU.  4096 MPC problems in mixed precision: 83 ms there, 23
+// here; a handful from host arrays to results 28 ms and 6.  16 waves rather
+// than 4: with one wave on a SIMD the same work took twice as long, bound by
+// instruction fetch.  Instances far smaller than the workgroup are no slower
+// for it (640 iterations of 4096 of them, general kernel and here: 16
+// variables 19.1 and 18.8 ms, 64 19.6 and 19.5, 256 22.4 and 20.8, in mixed
+// precision 18.9 and 18.5, 19.5 and 18.6, 22.8 and 19.8; of 64 of them, 3.7
+// to 4.1 and 1.1 to 1.3).
+//
+// The iterates are the general kernel's of 256 threads to the bit: each
+// product sums a row with one thread in row order, the norms and the weight's
+// update take their sums in its order, the Halpern averages its fused form.
+// (In mixed precision a last bit that differs turns FP32 roundings: other
+// orders moved results by 1e-10, single entries by 3e-8.)  The check's other
+// sums are grouped by the workgroup, so the residuals and objectives that it
+// reports, and a certificate's entries, may differ in their last bits.
 #include <math.h>
 
 #include <type_traits>
@@ -79,13 +88,36 @@ template <class T, int CAP>
 __device__ __forceinline__ void load_row(int a, int len, const T* val, const unsigned short* c16, const int* c32, int first,
                                          int zero, T (&v)[CAP], unsigned (&o)[CAP])
 {
+    if constexpr (sizeof(T) == 4) {
+        // Without a branch per entry (a missing one reads entry 0 and drops
+        // it): the branches' merges made one 64-byte vector of v, and every
+        // iteration then reloaded 256 bytes of it from scratch (4096 MPC
+        // problems: 54 ms, 23 without; 1024 instances of 256 variables 9.4 and
+        // 5.0, where the general kernel takes 5.9).  (The FP64 form spills
+        // less with the branches.)
+        int j[CAP];
+        if (c16) {
 #pragma unroll
-    for (int k = 0; k < CAP; ++k) {
-        v[k] = T(0);
-        o[k] = (unsigned)(zero * (int)sizeof(T));
-        if (k < len) {
-            v[k] = val[a + k];
-            o[k] = (unsigned)(local_col(c16, c32, a + k, first) * (int)sizeof(T));
+            for (int k = 0; k < CAP; ++k) j[k] = c16[k < len ? a + k : 0];
+        } else {
+#pragma unroll
+            for (int k = 0; k < CAP; ++k) j[k] = c32[k < len ? a + k : 0] - first;
+        }
+#pragma unroll
+        for (int k = 0; k < CAP; ++k) {
+            const T e = val[k < len ? a + k : 0];
+            v[k] = k < len ? e : T(0);
+            o[k] = (unsigned)((k < len ? j[k] : zero) * (int)sizeof(T));
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < CAP; ++k) {
+            v[k] = T(0);
+            o[k] = (unsigned)(zero * (int)sizeof(T));
+            if (k < len) {
+                v[k] = val[a + k];
+                o[k] = (unsigned)(local_col(c16, c32, a + k, first) * (int)sizeof(T));
+            }
         }
     }
 }
