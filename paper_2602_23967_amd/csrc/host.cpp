@@ -1144,6 +1144,7 @@ struct qp_batch {
     BatchDev B;
     hipStream_t stream = nullptr;
     bool own_stream = true;        // false: a stream lent by the caller (not destroyed)
+    SideStreams side;              // (with an arena: the arena's)
     hipEvent_t done = nullptr;
     double t_launch = 0.0;
     int64_t nnz_a = 0, nnz_q = 0;
@@ -1209,10 +1210,12 @@ void qp_batch_destroy(qp_batch* bt)
     if (!bt) return;
     if (bt->stream || bt->arena) {
         (void)hipStreamSynchronize(bt->stream);
+        (bt->arena ? *bt->arena->side : bt->side).wait();   // (after a launch that failed half-way)
         for (void* p : bt->allocs) (void)hipFreeAsync(p, bt->stream);
         (void)hipStreamSynchronize(bt->stream);
     }
     if (bt->done) (void)hipEventDestroy(bt->done);
+    bt->side.destroy();
     if (bt->stream && bt->own_stream) (void)hipStreamDestroy(bt->stream);
     delete bt;
 }
@@ -1230,6 +1233,37 @@ int qp_batch_create(int64_t count, const int64_t* var_off, const int64_t* row_of
 }  // extern "C"
 
 namespace pdhcg {
+
+bool SideStreams::make(int count)
+{
+    if (!fork && hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess) return false;
+    for (int i = 0; i < count; ++i) {
+        if (!s[i] && hipStreamCreateWithFlags(&s[i], hipStreamNonBlocking) != hipSuccess) return false;
+        if (!join[i] && hipEventCreateWithFlags(&join[i], hipEventDisableTiming) != hipSuccess) return false;
+    }
+    return true;
+}
+
+void SideStreams::wait()
+{
+    for (hipStream_t q : s)
+        if (q) (void)hipStreamSynchronize(q);
+}
+
+void SideStreams::destroy()
+{
+    wait();
+    for (hipStream_t& q : s) {
+        if (q) (void)hipStreamDestroy(q);
+        q = nullptr;
+    }
+    for (hipEvent_t& e : join) {
+        if (e) (void)hipEventDestroy(e);
+        e = nullptr;
+    }
+    if (fork) (void)hipEventDestroy(fork);
+    fork = nullptr;
+}
 
 int batch_create(hipStream_t lane, int64_t count, const int64_t* var_off, const int64_t* row_off,
                  const int64_t* Qp, const int32_t* Qj, const double* Qv,
@@ -1555,9 +1589,35 @@ int batch_launch(qp_batch* bt, const qp_params* params)
     bt->B.general_list = list + nc;
     bt->B.rest_count = (int)bt->count - nc - ng;
     bt->B.rest_list = split ? list + nc + ng : (bt->order ? bt->dorder : nullptr);
-    HIPCHK(launch_closed_solve(bt->B, P, bt->stream));
-    HIPCHK(launch_general_solve(bt->B, P, bt->stream));
-    HIPCHK(launch_batch_solve(bt->B, P, bt->shape, bt->stream));
+    // The kinds run at the same time, each on a stream of its own, as they did
+    // when one kernel took them all: one after the other a batch takes the sum
+    // of its longest instances (24 random QPs of 500 variables and 8 of 1500,
+    // 128 iterations: one kernel 19.0 ms, one after the other 21.4, at the same
+    // time 19.2; 1024 closed-form instances of 256 variables and 64 of 1200,
+    // 640 iterations: 12.6 to 14.5, 16.0 and 11.0).  The largest instances
+    // start first.
+    const int kinds = (nc > 0) + (ng > 0) + (bt->B.rest_count > 0);
+    SideStreams* side = bt->arena ? bt->arena->side : &bt->side;
+    hipError_t e = hipSuccess;
+    if (kinds < 2 || !side->make(kinds - 1)) side = nullptr;
+    if (side) {
+        e = hipEventRecord(side->fork, bt->stream);
+        for (int i = 0; i + 1 < kinds && e == hipSuccess; ++i) e = hipStreamWaitEvent(side->s[i], side->fork, 0);
+    }
+    int started = 0;
+    auto next = [&] {
+        const int i = started++;
+        return side && i > 0 ? side->s[i - 1] : bt->stream;
+    };
+    if (e == hipSuccess && bt->B.rest_count > 0) e = launch_batch_solve(bt->B, P, bt->shape, next());
+    if (e == hipSuccess && ng > 0) e = launch_general_solve(bt->B, P, next());
+    if (e == hipSuccess && nc > 0) e = launch_closed_solve(bt->B, P, next());
+    for (int i = 0; side && i + 1 < started; ++i) {
+        const hipError_t r = hipEventRecord(side->join[i], side->s[i]);
+        const hipError_t w = r == hipSuccess ? hipStreamWaitEvent(bt->stream, side->join[i], 0) : r;
+        if (e == hipSuccess) e = w;
+    }
+    HIPCHK(e);
     if (bt->done) HIPCHK(hipEventRecord(bt->done, bt->stream));
     return 0;
 }

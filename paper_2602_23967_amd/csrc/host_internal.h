@@ -12,18 +12,32 @@
 
 namespace pdhcg {
 
+// Streams beside a batch's own (default priority, no events' timing), on which
+// kernels of one launch that do not depend on each other run at the same
+// time.  Made when a launch first needs them; make() returns false where that
+// fails, and then the kernels follow each other on the one stream.
+struct SideStreams {
+    static constexpr int MAX = 2;
+    hipStream_t s[MAX] = {};
+    hipEvent_t fork = nullptr, join[MAX] = {};
+    bool make(int count);
+    void wait();      // for all work on them
+    void destroy();
+};
+
 // A region of device memory the library does not own (the static workspace of
 // qp_batch_solve_static): allocations are carved from it in 256-byte steps
 // and never freed; one that does not fit fails with QP_ERR_INVALID_ARG.
 struct Arena {
     char* base = nullptr;
     size_t cap = 0, used = 0;
+    SideStreams* side = nullptr;   // kept with the region, for one batch at a time
 };
 
 // qp_batch_create on a stream lent by the caller (NULL: the batch makes its
 // own).  With an arena, every device buffer of the batch comes from it, the
-// batch uses `lane` as given (NULL is the null stream) and creates no stream
-// or event: nothing is allocated on the device.
+// batch uses `lane` as given (NULL is the null stream) and the arena's side
+// streams, and creates no stream or event: nothing is allocated on the device.
 int batch_create(hipStream_t lane, int64_t count, const int64_t* var_off, const int64_t* row_off,
                  const int64_t* Qp, const int32_t* Qj, const double* Qv,
                  const int64_t* Ap, const int32_t* Aj, const double* Av,

@@ -24,6 +24,7 @@ namespace {
 constexpr int MAX_DEVICES = 64;
 std::mutex g_ws_mutex[MAX_DEVICES];
 void* g_ws_ptr[MAX_DEVICES];   // device address of `scratch` on each device (set once)
+SideStreams g_ws_side[MAX_DEVICES];   // made by the first call that needs them; with the mutex held
 
 // the workspace of the current device `dev`; call with g_ws_mutex[dev] held
 int ws_ptr(int dev, void** out)
@@ -57,6 +58,7 @@ extern "C" int qp_batch_solve_static(int64_t count, const int64_t* var_off, cons
     Arena arena;
     arena.base = static_cast<char*>(base);
     arena.cap = (size_t)QP_STATIC_WORKSPACE_BYTES;
+    arena.side = &g_ws_side[dev];
     qp_batch* bt = nullptr;
     int rc = batch_create(static_cast<hipStream_t>(stream), count, var_off, row_off, Q_rowptr, Q_col, Q_val,
                           A_rowptr, A_col, A_val, c, b, sense, lb, ub, &bt, &arena);
