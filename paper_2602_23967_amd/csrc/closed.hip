@@ -37,7 +37,7 @@ namespace pdhcg {
 // ---- LDS of a workgroup: the CU's 160 KB, in doubles -----------------------------
 
 constexpr int LDS_ALL = 160 * 1024 / 8;
-constexpr int LDS_RED = RED_SLOTS * WAVES;                                // wg_sum's buffer
+constexpr int LDS_RED = RED_SLOTS * (REG_MAX / 64);                                // wg_sum's buffer
 constexpr int LDS_OP = REG_MAX + 2;                                       // an operand and its zero entry
 // each thread's cost, box and anchor; mixed precision (T = float): and the
 // reference point and its products
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(REG_MAX) void k_closed_solve(BatchDev B, BatchParam
                 if (tid == 0) { s->k = k; s->t = t; }
                 __syncthreads();
                 const int restart = uniform_int(
-                    one_cu_check<F32, false>((unsigned long long)__builtin_amdgcn_kernarg_segment_ptr(), b, red, s));
+                    one_cu_check<F32, false, REG_MAX>((unsigned long long)__builtin_amdgcn_kernarg_segment_ptr(), b, red, s));
                 status = uniform_int(s->status);
                 if (status) break;
                 seen = true;
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(REG_MAX) void k_closed_solve(BatchDev B, BatchParam
                         }
                     }
                     __syncthreads();
-                    wg_sum<7, (1u << 2) | (1u << 5)>(a, red);   // its barrier also publishes sy
+                    wg_sum<REG_MAX, 7, (1u << 2) | (1u << 5)>(a, red);   // its barrier also publishes sy
                     if (tid == 0) {
                         s->ndx2 = a[0];
                         s->ndy2 = a[1];

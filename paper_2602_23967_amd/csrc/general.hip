@@ -10,6 +10,14 @@
 // inner step with its share of the outer one.  What is left is bound by
 // instruction issue: 16 waves of some 700 instructions a step.
 //
+// An instance of at most 256 variables and rows takes a workgroup of 256
+// threads and a quarter of the CU's LDS, so that four share the CU: most of
+// 1024 threads would only take part in the barriers and the sums, and a batch
+// that fills the chip was slower than in the general kernel, which kept four
+// instances on a CU (128 iterations of 1024 random QPs, general kernel, 1024
+// threads and 256: 128 variables 6.2, 8.1 and 2.4 ms, 256 9.6, 8.7 and 3.0;
+// 48 of them 4.4, 2.1 and 1.6, 4.8, 2.3 and 1.8).
+//
 // The variables are dealt to the threads by the length of their row of Q,
 // longest first: a wave's product takes as long as its longest row, so in
 // index order most of its lanes would wait (random QPs: 11 entries a row on
@@ -28,19 +36,24 @@
 namespace pdhcg {
 
 constexpr int REG_Q = ONE_CU_REG_Q;     // entries of a row of Q in registers
-constexpr int REST_Q = ONE_CU_REST_Q;   // places in LDS for the longer rows' other entries
-constexpr int LDS_ALL = 160 * 1024 / 8;
-constexpr int OP = REG_MAX + 2;      // an operand and its zero entry
-// LDS in doubles: reductions, three operands, state, the deal of the variables
-constexpr int AT_RED = 0;
-constexpr int AT_OPS = AT_RED + RED_SLOTS * WAVES;        // (the check uses the first operand's space)
-constexpr int AT_STEP = AT_OPS + 3 * OP;                  // two buffers of the step's reductions
-constexpr int AT_STATE = AT_STEP + 2 * 16 * WAVES;
-constexpr int AT_MISC = AT_STATE + (int)((sizeof(ClosedState) + 7) / 8);
-constexpr int AT_DEAL = AT_MISC + 16;                     // place of a variable, variable of a place (16 bits each)
-constexpr int AT_REST = AT_DEAL + 2 * REG_MAX / 4;
-constexpr int AT_A = AT_REST + REST_Q + REST_Q / 4;
-constexpr int A_PLACES = ((LDS_ALL - AT_A) * 8 / 10) & ~63;
+// A workgroup of T threads and its share of the CU's 160 KB of LDS, in
+// doubles: reductions, three operands, state, the deal of the variables, and
+// places (a value and a 16-bit operand index each) for what the registers do
+// not hold of Q and, after it, A
+template <int T>
+struct Cu {
+    static constexpr int WAVES = T / 64;
+    static constexpr int ALL = 160 * 1024 / 8 / (REG_MAX / T);
+    static constexpr int OP = T + 2;                               // an operand and its zero entry
+    static constexpr int AT_OPS = RED_SLOTS * WAVES;               // (the check uses the first operand's space)
+    static constexpr int AT_STEP = AT_OPS + 3 * OP;                // two buffers of the step's reductions
+    static constexpr int AT_STATE = AT_STEP + 2 * 16 * WAVES;
+    static constexpr int AT_MISC = AT_STATE + (int)((sizeof(ClosedState) + 7) / 8);
+    static constexpr int AT_DEAL = AT_MISC + 16;                   // place of a variable, variable of a place (16 bits each)
+    static constexpr int AT_MAT = AT_DEAL + 2 * T / 4;
+    static constexpr int PLACES = ((ALL - AT_MAT) * 8 / 10) & ~63;
+};
+static_assert(ONE_CU_REST_Q <= Cu<REG_MAX>::PLACES && ONE_CU_SMALL_Q <= Cu<ONE_CU_SMALL>::PLACES, "Q has to fit");
 
 // v of the lane `CTRL` names, lanes without a source 0
 template <int CTRL>
@@ -71,14 +84,15 @@ __device__ __forceinline__ double row_min(double v)
 // Four values over the workgroup, in every thread: sums, but the last a
 // minimum where MIN3.  One barrier.  The kernel is bound by instruction
 // issue (4 waves on a SIMD), so a wave reduces no further than its rows of
-// 16 lanes; then every wave reads the 64 rows' partials, 16 lanes for each
+// 16 lanes; then every wave reads all rows' partials, 16 lanes for each
 // value.  live: the wave has a variable (otherwise its values are the
 // identities).
-template <bool MIN3>
+template <int T, bool MIN3>
 __device__ __forceinline__ void step_sum(double (&v)[4], bool live, double* lds)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    static_assert(WAVES == 16, "a value's waves fill a row of 16 lanes");
+    constexpr int WAVES = T / 64, PER = WAVES / 4;   // partials that a lane reads
+    static_assert(PER == 1 || PER == 4, "a value's partials are shared by 16 lanes");
     if (live) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] = MIN3 && j == 3 ? row_min(v[j]) : (MIN3 && j == 2 ? 0.0 : row_sum(v[j]));
@@ -88,10 +102,15 @@ __device__ __forceinline__ void step_sum(double (&v)[4], bool live, double* lds)
         for (int j = 0; j < 4; ++j) lds[(j * WAVES + wave) * 4 + (lane >> 4)] = v[j];
     }
     __syncthreads();
-    const double *q = lds + 4 * lane, a0 = q[0], a1 = q[1], a2 = q[2], a3 = q[3];
-    double r = row_sum((a0 + a1) + (a2 + a3));
+    const double* q = lds + PER * lane;
+    double sum = q[0], least = q[0];
+    if constexpr (PER == 4) {
+        sum = (q[0] + q[1]) + (q[2] + q[3]);
+        least = lesser(lesser(q[0], q[1]), lesser(q[2], q[3]));
+    }
+    double r = row_sum(sum);
     if constexpr (MIN3) {
-        const double mn = row_min(lesser(lesser(a0, a1), lesser(a2, a3)));
+        const double mn = row_min(least);
         r = lane >= 48 ? mn : r;
     }
     const long long b = __double_as_longlong(r);
@@ -111,20 +130,25 @@ __device__ __forceinline__ int longest(int len)
     return uniform_int(most);
 }
 
-// the wave's share of `total` places: `base` and how many entries of each of
-// its 64 rows fit; the waves' shares follow each other
+// the wave's share of the places [first, total): `base` and how many entries
+// of each of its 64 rows fit; the waves' shares follow each other up to `end`
 struct Share {
-    int base, wide;
+    int base, wide, end;
 };
-__device__ __forceinline__ Share share(int want, int total, int* widths)
+template <int T>
+__device__ __forceinline__ Share share(int want, int first, int total, int* widths)
 {
     const int wave = uniform_int(threadIdx.x >> 6);
     if ((threadIdx.x & 63) == 0) widths[wave] = want;
     __syncthreads();
-    int base = 0;
-    for (int w = 0; w < wave; ++w) base += 64 * widths[w];
+    int base = first, end = first;
+    for (int w = 0; w < T / 64; ++w) {
+        if (w == wave) base = end;
+        end += 64 * widths[w];
+    }
     Share p;
     p.base = uniform_int(base < total ? base : total);
+    p.end = uniform_int(end < total ? end : total);
     const int fit = (total - p.base) / 64;
     p.wide = uniform_int(want < fit ? want : fit);
     __syncthreads();
@@ -212,6 +236,7 @@ struct Inner {
     long long max_inner;
     long long steps = 0, products = 0;
 };
+template <int T>
 __device__ __forceinline__ void inner_solve(Inner& s, const RowQ& Q, bool on, bool live, double l, double u, double rhs,
                                             double& xt, double& g, double (&st)[4], double* sp, double* sxt, double* redh,
                                             double* redu)
@@ -239,7 +264,7 @@ __device__ __forceinline__ void inner_solve(Inner& s, const RowQ& Q, bool on, bo
             }
         }
         ++s.products;
-        step_sum<true>(hs, live, redh);
+        step_sum<T, true>(hs, live, redh);
         if (uniform_int(!(hs[0] > 0.0))) break;
         const double af = hs[3] < 0.0 ? 0.0 : hs[3];
         const double acg = hs[1] / hs[0];
@@ -280,7 +305,7 @@ __device__ __forceinline__ void inner_solve(Inner& s, const RowQ& Q, bool on, bo
                 }
             }
         }
-        step_sum<false>(us, live, redu);
+        step_sum<T, false>(us, live, redu);
         if (kind == STEP_CG) gam = uniform(us[3] / hs[0]);
         st[0] = us[0];
         done = uniform_int(sqrt(us[0]) <= s.eps || s.steps >= s.max_inner);
@@ -309,37 +334,40 @@ __device__ __forceinline__ void deal_rows(int n, const int* rp, int* lens, unsig
     __syncthreads();
 }
 
-__global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchParams P)
+template <int T>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_general_solve(BatchDev B, BatchParams P)
 {
-    __shared__ double sh[LDS_ALL];
-    double* red = sh + AT_RED;
-    double* redh = sh + AT_STEP;
-    double* redu = redh + 16 * WAVES;
-    double* sp = sh + AT_OPS;              // direction; x_bar
-    double* sxt = sh + AT_OPS + OP;        // x_T
-    double* sy = sh + AT_OPS + 2 * OP;     // y
-    ClosedState* s = reinterpret_cast<ClosedState*>(sh + AT_STATE);
-    int* misc = reinterpret_cast<int*>(sh + AT_MISC);       // [0] instance, [16..31] widths
-    unsigned short* place = reinterpret_cast<unsigned short*>(sh + AT_DEAL);
-    unsigned short* var = place + REG_MAX;
-    double* lqv = sh + AT_REST;
-    unsigned short* lqo = reinterpret_cast<unsigned short*>(lqv + REST_Q);
-    double* lav = sh + AT_A;
-    unsigned short* lao = reinterpret_cast<unsigned short*>(lav + A_PLACES);
+    typedef Cu<T> L;
+    __shared__ double sh[L::ALL];
+    double* red = sh;
+    double* redh = sh + L::AT_STEP;
+    double* redu = redh + 16 * L::WAVES;
+    double* sp = sh + L::AT_OPS;              // direction; x_bar
+    double* sxt = sh + L::AT_OPS + L::OP;     // x_T
+    double* sy = sh + L::AT_OPS + 2 * L::OP;  // y
+    ClosedState* s = reinterpret_cast<ClosedState*>(sh + L::AT_STATE);
+    int* misc = reinterpret_cast<int*>(sh + L::AT_MISC);       // [0] instance, [16..31] widths
+    unsigned short* place = reinterpret_cast<unsigned short*>(sh + L::AT_DEAL);
+    unsigned short* var = place + T;
+    double* lv = sh + L::AT_MAT;
+    unsigned short* lo = reinterpret_cast<unsigned short*>(lv + L::PLACES);
     const int tid = threadIdx.x;
 
+    const int count = T == REG_MAX ? B.general_count : B.small_count;
+    const int* list = T == REG_MAX ? B.general_list : B.small_list;
+
     for (;;) {
-        if (tid == 0) misc[0] = atomicAdd(B.queue + 2, 1);
+        if (tid == 0) misc[0] = atomicAdd(B.queue + (T == REG_MAX ? 2 : 3), 1);
         __syncthreads();
         const int at = uniform_int(misc[0]);
-        if (at >= B.general_count) return;
-        const int b = uniform_int(B.general_list[at]);
+        if (at >= count) return;
+        const int b = uniform_int(list[at]);
         const unsigned long long t_start = wall_clock64();
         const ClosedInst in = closed_instance(B, b);
         const int v0 = in.v0, r0 = in.r0, n = in.n, m = in.m, unb = in.unb;
         const double normq = uniform(B.normq[b]);
         const bool xon = tid < n, yon = tid < m;
-        deal_rows(n, B.qrp + v0, reinterpret_cast<int*>(sh + AT_OPS), place, var);
+        deal_rows(n, B.qrp + v0, reinterpret_cast<int*>(sh + L::AT_OPS), place, var);
         const int vi = v0 + (xon ? (int)var[tid] : 0), ri = r0 + (yon ? tid : 0);
         const int qa = xon ? B.qrp[vi] : 0, ql = xon ? B.qrp[vi + 1] - qa : 0;
         const int ta = xon ? B.trp[vi] : 0, tl = xon ? B.trp[vi + 1] - ta : 0;
@@ -348,15 +376,15 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
         const bool live = uniform_int(tid & ~63) < n, any = uniform_int(tid & ~63) < (n > m ? n : m);
         RowQ Q;
         Q.most = qmost;
-        const Share qs = share(qmost > REG_Q ? qmost - REG_Q : 0, REST_Q, misc + 16);
-        const Share as = share(amost, A_PLACES, misc + 16);
+        const Share qs = share<T>(qmost > REG_Q ? qmost - REG_Q : 0, 0, L::PLACES, misc + 16);
+        const Share as = share<T>(amost, qs.end, L::PLACES, misc + 16);
         Q.base = qs.base;
         Q.wide = qs.wide;
-        Q.lv = lqv;
-        Q.lo = lqo;
-        fill(qs, qa, ql, REG_Q, B.qval, B.qcol16, B.qcol, v0, place, n, lqv, lqo);
-        fill(as, aa, al, 0, B.aval, B.acol16, B.acol, v0, place, n, lav, lao);
-        for (int i = tid; i < 3 * OP; i += REG_MAX) sh[AT_OPS + i] = 0.0;
+        Q.lv = lv;
+        Q.lo = lo;
+        fill(qs, qa, ql, REG_Q, B.qval, B.qcol16, B.qcol, v0, place, n, lv, lo);
+        fill(as, aa, al, 0, B.aval, B.acol16, B.acol, v0, place, n, lv, lo);
+        for (int i = tid; i < 3 * L::OP; i += T) sh[L::AT_OPS + i] = 0.0;
         __syncthreads();
         double x = 0.0, y = 0.0, xt = 0.0;
         if (xon) {
@@ -388,7 +416,7 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
                 if (tid == 0) { s->k = k; s->t = t; }
                 __syncthreads();
                 const int restart = uniform_int(
-                    one_cu_check<false, true>((unsigned long long)__builtin_amdgcn_kernarg_segment_ptr(), b, red, s));
+                    one_cu_check<false, true, T>((unsigned long long)__builtin_amdgcn_kernarg_segment_ptr(), b, red, s));
                 status = uniform_int(s->status);
                 if (status) break;
                 if (restart) {
@@ -434,11 +462,11 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
                         st[2] = f.phit * f.phi;
                     }
                 }
-                step_sum<false>(st, live, redu);
+                step_sum<T, false>(st, live, redu);
                 if (isinf(eps) && P.eps_fixed <= 0.0) eps = uniform(fmax(P.gamma_inner * sqrt(st[0]), P.eps_min));
                 cg.eps = P.eps_fixed > 0.0 ? P.eps_fixed : eps;
                 cg.steps = 0;
-                inner_solve(cg, Q, xon, live, l, u, rhs, xt, g, st, sp, sxt, redh, redu);
+                inner_solve<T>(cg, Q, xon, live, l, u, rhs, xt, g, st, sp, sxt, redh, redu);
                 inner_total += cg.steps;
                 // x_bar
                 if (xon) {
@@ -454,7 +482,7 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
                     const int f = as.base + (tid & 63);
                     double ax = 0.0;
 #pragma unroll 4
-                    for (int q = 0; q < as.wide; ++q) ax += lav[f + 64 * q] * sp[lao[f + 64 * q]];
+                    for (int q = 0; q < as.wide; ++q) ax += lv[f + 64 * q] * sp[lo[f + 64 * q]];
                     for (int q = as.wide; q < al; ++q) ax += B.aval[aa + q] * sp[place[local_col(B.acol16, B.acol, aa + q, v0)]];
                     if (yon) {
                         lc = B.lc[ri];
@@ -473,7 +501,7 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
                     if (store) B.xt[vi] = xt;
                 }
                 double mv[4] = {dx * dx, dy * dy, 0.0, 0.0};
-                step_sum<false>(mv, any, redh);   // its barrier also publishes y
+                step_sum<T, false>(mv, any, redh);   // its barrier also publishes y
                 if (P.eps_fixed <= 0.0)
                     eps = uniform(fmin(eps, fmax(P.gamma_inner * omega * sqrt(mv[0]) / tau, P.eps_min)));
                 if (store) {   // the certificate pieces
@@ -491,7 +519,7 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
                         a[3] = fabs(di);
                         a[4] = B.c[vi] * di;
                     }
-                    wg_sum<5, 1u | (1u << 3)>(a, red);
+                    wg_sum<T, 5, 1u | (1u << 3)>(a, red);
                     if (tid == 0) {
                         s->ytil_max = a[0]; s->ptil_sum = a[1]; s->ptil_abs = a[2];
                         s->d_max = a[3];
@@ -534,41 +562,41 @@ __global__ __launch_bounds__(REG_MAX) void k_general_solve(BatchDev B, BatchPara
 // and 363 launch by launch.
 __global__ __launch_bounds__(REG_MAX) void k_single_solve(DevState S, CoopRun R)
 {
-    __shared__ double sh[LDS_ALL];
-    double* red = sh + AT_RED;
-    double* redh = sh + AT_STEP;
-    double* redu = redh + 16 * WAVES;
-    double* sp = sh + AT_OPS;
-    double* sxt = sh + AT_OPS + OP;
-    double* sy = sh + AT_OPS + 2 * OP;
-    int* misc = reinterpret_cast<int*>(sh + AT_MISC);
-    unsigned short* place = reinterpret_cast<unsigned short*>(sh + AT_DEAL);
-    unsigned short* var = place + REG_MAX;
-    double* lqv = sh + AT_REST;
-    unsigned short* lqo = reinterpret_cast<unsigned short*>(lqv + REST_Q);
-    double* lav = sh + AT_A;
-    unsigned short* lao = reinterpret_cast<unsigned short*>(lav + A_PLACES);
+    constexpr int T = REG_MAX;
+    typedef Cu<T> L;
+    __shared__ double sh[L::ALL];
+    double* red = sh;
+    double* redh = sh + L::AT_STEP;
+    double* redu = redh + 16 * L::WAVES;
+    double* sp = sh + L::AT_OPS;              // direction; x_bar
+    double* sxt = sh + L::AT_OPS + L::OP;     // x_T
+    double* sy = sh + L::AT_OPS + 2 * L::OP;  // y
+    int* misc = reinterpret_cast<int*>(sh + L::AT_MISC);       // [0] instance, [16..31] widths
+    unsigned short* place = reinterpret_cast<unsigned short*>(sh + L::AT_DEAL);
+    unsigned short* var = place + T;
+    double* lv = sh + L::AT_MAT;
+    unsigned short* lo = reinterpret_cast<unsigned short*>(lv + L::PLACES);
     const int tid = threadIdx.x, n = S.n, m = S.m;
     const bool xon = tid < n, yon = tid < m;
     const bool live = uniform_int(tid & ~63) < n, any = uniform_int(tid & ~63) < (n > m ? n : m);
-    deal_rows(n, S.Q.rowptr, reinterpret_cast<int*>(sh + AT_OPS), place, var);
+    deal_rows(n, S.Q.rowptr, reinterpret_cast<int*>(sh + L::AT_OPS), place, var);
     const int vi = xon ? (int)var[tid] : 0, ri = yon ? tid : 0;
     const int qa = xon ? S.Q.rowptr[vi] : 0, ql = xon ? S.Q.rowptr[vi + 1] - qa : 0;
     const int ta = xon ? S.AT.rowptr[vi] : 0, tl = xon ? S.AT.rowptr[vi + 1] - ta : 0;
     const int aa = yon ? S.A.rowptr[ri] : 0, al = yon ? S.A.rowptr[ri + 1] - aa : 0;
     const int qmost = longest(ql), amost = longest(al);
-    const Share qs = share(qmost > REG_Q ? qmost - REG_Q : 0, REST_Q, misc + 16);
-    const Share as = share(amost, A_PLACES, misc + 16);
-    fill(qs, qa, ql, REG_Q, S.Q.val, nullptr, S.Q.col, 0, place, n, lqv, lqo);
-    fill(as, aa, al, 0, S.A.val, nullptr, S.A.col, 0, place, n, lav, lao);
+    const Share qs = share<T>(qmost > REG_Q ? qmost - REG_Q : 0, 0, L::PLACES, misc + 16);
+    const Share as = share<T>(amost, qs.end, L::PLACES, misc + 16);
+    fill(qs, qa, ql, REG_Q, S.Q.val, nullptr, S.Q.col, 0, place, n, lv, lo);
+    fill(as, aa, al, 0, S.A.val, nullptr, S.A.col, 0, place, n, lv, lo);
     RowQ Q;
     Q.most = qmost;
     Q.base = qs.base;
     Q.wide = qs.wide;
-    Q.lv = lqv;
-    Q.lo = lqo;
+    Q.lv = lv;
+    Q.lo = lo;
     Q.load(qa, ql, S.Q.val, nullptr, S.Q.col, 0, place, n);
-    for (int i = tid; i < 3 * OP; i += REG_MAX) sh[AT_OPS + i] = 0.0;
+    for (int i = tid; i < 3 * L::OP; i += T) sh[L::AT_OPS + i] = 0.0;
     __syncthreads();
 
     const Ctrl* c0 = S.ctrl;
@@ -618,12 +646,12 @@ __global__ __launch_bounds__(REG_MAX) void k_single_solve(DevState S, CoopRun R)
                 st[2] = f.phit * f.phi;
             }
         }
-        step_sum<false>(st, live, redu);
+        step_sum<T, false>(st, live, redu);
         if (exact && isinf(eps) && eps_fixed <= 0.0) eps = uniform(fmax(gamma_inner * sqrt(st[0]), eps_min));
         g_it = it;
         cg.eps = eps_fixed > 0.0 ? eps_fixed : eps;
         cg.steps = 0;
-        inner_solve(cg, Q, xon, live, l, u, rhs, xt, g, st, sp, sxt, redh, redu);
+        inner_solve<T>(cg, Q, xon, live, l, u, rhs, xt, g, st, sp, sxt, redh, redu);
         inner_total += cg.steps;
         res = sqrt(st[0]);
         if (R.sub) break;
@@ -640,7 +668,7 @@ __global__ __launch_bounds__(REG_MAX) void k_single_solve(DevState S, CoopRun R)
             const int f = as.base + (tid & 63);
             double ax = 0.0;
 #pragma unroll 4
-            for (int q = 0; q < as.wide; ++q) ax += lav[f + 64 * q] * sp[lao[f + 64 * q]];
+            for (int q = 0; q < as.wide; ++q) ax += lv[f + 64 * q] * sp[lo[f + 64 * q]];
             for (int q = as.wide; q < al; ++q) ax += S.A.val[aa + q] * sp[place[S.A.col[aa + q]]];
             if (yon) {
                 lc = S.lc[ri];
@@ -657,7 +685,7 @@ __global__ __launch_bounds__(REG_MAX) void k_single_solve(DevState S, CoopRun R)
             x = halpern ? w * ((1.0 + th) * xt - th * x) + wa * S.xa[vi] : xt;
         }
         double mv[4] = {dx * dx, dy * dy, 0.0, 0.0};
-        step_sum<false>(mv, any, redh);   // its barrier also publishes y
+        step_sum<T, false>(mv, any, redh);   // its barrier also publishes y
         ndx2 = mv[0];
         ndy2 = mv[1];
         if (eps_fixed <= 0.0) eps = uniform(fmin(eps, fmax(gamma_inner * omega * sqrt(ndx2) / tau, eps_min)));
@@ -677,7 +705,7 @@ __global__ __launch_bounds__(REG_MAX) void k_single_solve(DevState S, CoopRun R)
                 a[3] = fabs(di);
                 a[4] = S.c[vi] * di;
             }
-            wg_sum<5, 1u | (1u << 3)>(a, red);
+            wg_sum<T, 5, 1u | (1u << 3)>(a, red);
 #pragma unroll
             for (int j = 0; j < 5; ++j) cert[j] = a[j];
         }
@@ -725,8 +753,15 @@ hipError_t launch_single_solve(const DevState& S, const CoopRun& R, hipStream_t 
 hipError_t launch_general_solve(const BatchDev& B, const BatchParams& P, hipStream_t s)
 {
     if (B.general_count < 1) return hipSuccess;
-    const int grid = one_cu_grid(B.general_count);
-    k_general_solve<<<grid, REG_MAX, 0, s>>>(B, P);
+    k_general_solve<REG_MAX><<<one_cu_grid(B.general_count), REG_MAX, 0, s>>>(B, P);
+    return hipGetLastError();
+}
+
+hipError_t launch_small_solve(const BatchDev& B, const BatchParams& P, hipStream_t s)
+{
+    if (B.small_count < 1) return hipSuccess;
+    constexpr int T = ONE_CU_SMALL;
+    k_general_solve<T><<<one_cu_grid(B.small_count, REG_MAX / T), T, 0, s>>>(B, P);
     return hipGetLastError();
 }
 

@@ -235,19 +235,26 @@ int64_t longest_row(int64_t rows, const int64_t* rp)
     return l;
 }
 
-// A Q with n rows at rp whose rows the kernels of general.hip hold: dealt by
-// length to waves of 64 rows, what is past the registers has a place in LDS.
-// (A row read from memory in every step is what the general kernels do, with
-// more workgroups or threads.)
-bool one_cu_fits(int64_t n, int64_t m, const int64_t* rp)
+// LDS places that the rows of a Q with n rows at rp take in the kernels of
+// general.hip: dealt by length to waves of 64 rows, what is past the
+// registers.  (A row read from memory in every step is what the general
+// kernels do, with more workgroups or threads.)
+int64_t q_places(int64_t n, const int64_t* rp)
 {
-    if (n < 1 || n > ONE_CU_MAX || m > ONE_CU_MAX) return false;
     std::vector<int64_t> len(n);
     for (int64_t i = 0; i < n; ++i) len[i] = rp[i + 1] - rp[i];
     std::sort(len.begin(), len.end(), [](int64_t a, int64_t b) { return a > b; });
     int64_t places = 0;
     for (int64_t i = 0; i < n; i += 64) places += 64 * std::max<int64_t>(0, len[i] - ONE_CU_REG_Q);
-    return places <= ONE_CU_REST_Q;
+    return places;
+}
+bool one_cu_fits(int64_t n, int64_t m, const int64_t* rp)
+{
+    return n >= 1 && n <= ONE_CU_MAX && m <= ONE_CU_MAX && q_places(n, rp) <= ONE_CU_REST_Q;
+}
+bool small_fits(int64_t n, int64_t m, const int64_t* rp)
+{
+    return n >= 1 && n <= ONE_CU_SMALL && m <= ONE_CU_SMALL && q_places(n, rp) <= ONE_CU_SMALL_Q;
 }
 
 // prepares the one-launch iteration where the problem fits it (single, or coop.ns > 0)
@@ -1157,11 +1164,11 @@ struct qp_batch {
     // (0 index order, 1 largest instance first; dorder holds that permutation)
     // Each of the two queue orders lists the instances that the default
     // shapes give to the kernels of closed.hip (nclosed of them) and
-    // general.hip (ngeneral) first, then the others; dorder is the second
-    // order for the kernels of other shapes, which take all instances
+    // general.hip (ngeneral, nsmall) first, then the others; dorder is the
+    // second order for the kernels of other shapes, which take all instances
     int shape = pdhcg::BATCH_SHAPE_DEFAULT, order = 1;
     const int *dorder = nullptr, *dsplit[2] = {nullptr, nullptr};
-    int nclosed = 0, ngeneral = 0;
+    int nclosed = 0, ngeneral = 0, nsmall = 0;
     int solved = 0;
     double setup_seconds = 0.0, solve_seconds = 0.0;
     mutable ReadAhead ahead;   // results of the last solve already on the host
@@ -1435,7 +1442,7 @@ int batch_create(hipStream_t lane, int64_t count, const int64_t* var_off, const 
     double** mv[] = {&B.y, &B.ya, &B.yt, &B.ytil, &B.yref, &B.axref};
     for (double** p : mv)
         if ((rc = balloc(bt, p, (size_t)m))) return bail(rc);
-    if ((rc = balloc(bt, &B.queue, 3)) || (rc = balloc(bt, &B.out, (size_t)count))) return bail(rc);
+    if ((rc = balloc(bt, &B.queue, 4)) || (rc = balloc(bt, &B.out, (size_t)count))) return bail(rc);
     {
         // largest instance first (nonzeros of A and Q plus n + m), ties in
         // index order: a longest-processing-time-first queue, so the launch
@@ -1451,10 +1458,16 @@ int batch_create(hipStream_t lane, int64_t count, const int64_t* var_off, const 
             return var_off[i + 1] - var_off[i] <= ONE_CU_MAX && row_off[i + 1] - row_off[i] <= ONE_CU_MAX;
         };
         auto closed = [&](int i) { return !qgen[i] && one_cu(i); };
-        std::vector<char> fits(count, 0);
-        for (int64_t i = 0; i < count; ++i)
-            fits[i] = qgen[i] && one_cu_fits(var_off[i + 1] - var_off[i], row_off[i + 1] - row_off[i], Qp + var_off[i]);
-        auto general = [&](int i) { return fits[i] != 0; };
+        std::vector<char> fits(count, 0);   // 1: a CU with three others of its kind, 2: a CU
+        for (int64_t i = 0; i < count; ++i) {
+            const int64_t ni = var_off[i + 1] - var_off[i], mi = row_off[i + 1] - row_off[i];
+            const int64_t* rp = Qp + var_off[i];
+            if (!qgen[i]) continue;
+            if (small_fits(ni, mi, rp)) fits[i] = 1;
+            else if (one_cu_fits(ni, mi, rp) && (mi <= ONE_CU_SMALL || ni >= ONE_CU_MANY_ROWS)) fits[i] = 2;
+        }
+        auto general = [&](int i) { return fits[i] == 2; };
+        auto smaller = [&](int i) { return fits[i] == 1; };
         std::vector<int> lists(perm);   // dorder, then the two split orders
         for (int64_t i = 0; i < count; ++i) lists.push_back((int)i);
         lists.insert(lists.end(), perm.begin(), perm.end());
@@ -1462,7 +1475,9 @@ int batch_create(hipStream_t lane, int64_t count, const int64_t* var_off, const 
             const auto first = lists.begin() + o * count, end = first + count;
             const auto second = std::stable_partition(first, end, closed);
             bt->nclosed = (int)(second - first);
-            bt->ngeneral = (int)(std::stable_partition(second, end, general) - second);
+            const auto third = std::stable_partition(second, end, general);
+            bt->ngeneral = (int)(third - second);
+            bt->nsmall = (int)(std::stable_partition(third, end, smaller) - third);
         }
         // (a batch in the static workspace keeps its schedule: one list, so
         // the same batches fit as with a plain order)
@@ -1576,19 +1591,22 @@ int batch_launch(qp_batch* bt, const qp_params* params)
     P.mprgp_gamma = p.mprgp_gamma; P.abar_scale = p.mprgp_abar_scale; P.max_inner = p.max_inner;
     bt->t_launch = now_s();
     bt->ahead.drop();
-    HIPCHK(hipMemsetAsync(bt->B.queue, 0, 3 * sizeof(int), bt->stream));
+    HIPCHK(hipMemsetAsync(bt->B.queue, 0, 4 * sizeof(int), bt->stream));
     // The default shapes' small instances have kernels of their own; an
     // instance's route never depends on the others in the batch.
     const bool split = bt->shape == BATCH_SHAPE_DEFAULT || bt->shape == BATCH_SHAPE_GENERAL_DEFAULT;
     const int nc = split ? bt->nclosed : 0;
-    const int ng = split && p.precision == QP_PRECISION_FP64 ? bt->ngeneral : 0;
+    const bool inner = split && p.precision == QP_PRECISION_FP64;
+    const int ng = inner ? bt->ngeneral : 0, ns = inner ? bt->nsmall : 0;
     const int* list = bt->dsplit[bt->order];
     bt->B.closed_count = nc;
     bt->B.closed_list = list;
     bt->B.general_count = ng;
     bt->B.general_list = list + nc;
-    bt->B.rest_count = (int)bt->count - nc - ng;
-    bt->B.rest_list = split ? list + nc + ng : (bt->order ? bt->dorder : nullptr);
+    bt->B.small_count = ns;
+    bt->B.small_list = list + nc + ng;
+    bt->B.rest_count = (int)bt->count - nc - ng - ns;
+    bt->B.rest_list = split ? list + nc + ng + ns : (bt->order ? bt->dorder : nullptr);
     // The kinds run at the same time, each on a stream of its own, as they did
     // when one kernel took them all: one after the other a batch takes the sum
     // of its longest instances (24 random QPs of 500 variables and 8 of 1500,
@@ -1596,7 +1614,7 @@ int batch_launch(qp_batch* bt, const qp_params* params)
     // time 19.2; 1024 closed-form instances of 256 variables and 64 of 1200,
     // 640 iterations: 12.6 to 14.5, 16.0 and 11.0).  The largest instances
     // start first.
-    const int kinds = (nc > 0) + (ng > 0) + (bt->B.rest_count > 0);
+    const int kinds = (nc > 0) + (ng > 0) + (ns > 0) + (bt->B.rest_count > 0);
     SideStreams* side = bt->arena ? bt->arena->side : &bt->side;
     hipError_t e = hipSuccess;
     if (kinds < 2 || !side->make(kinds - 1)) side = nullptr;
@@ -1611,6 +1629,7 @@ int batch_launch(qp_batch* bt, const qp_params* params)
     };
     if (e == hipSuccess && bt->B.rest_count > 0) e = launch_batch_solve(bt->B, P, bt->shape, next());
     if (e == hipSuccess && ng > 0) e = launch_general_solve(bt->B, P, next());
+    if (e == hipSuccess && ns > 0) e = launch_small_solve(bt->B, P, next());
     if (e == hipSuccess && nc > 0) e = launch_closed_solve(bt->B, P, next());
     for (int i = 0; side && i + 1 < started; ++i) {
         const hipError_t r = hipEventRecord(side->join[i], side->s[i]);

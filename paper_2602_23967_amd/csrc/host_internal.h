@@ -17,7 +17,7 @@ namespace pdhcg {
 // time.  Made when a launch first needs them; make() returns false where that
 // fails, and then the kernels follow each other on the one stream.
 struct SideStreams {
-    static constexpr int MAX = 2;
+    static constexpr int MAX = 3;
     hipStream_t s[MAX] = {};
     hipEvent_t fork = nullptr, join[MAX] = {};
     bool make(int count);

@@ -1,6 +1,7 @@
 // one_cu.h -- what the kernels share that solve one instance of a batch with
-// a workgroup of 1024 threads on a CU of its own (closed.hip, general.hip):
-// reductions, the instance's ranges and state, the check.
+// a workgroup that holds it on a CU (closed.hip, general.hip), in most of them
+// one of 1024 threads with the CU to itself: reductions, the instance's ranges
+// and state, the check.
 #pragma once
 
 #include <math.h>
@@ -13,7 +14,6 @@
 namespace pdhcg {
 
 constexpr int REG_MAX = ONE_CU_MAX;   // variables, rows, threads
-constexpr int WAVES = REG_MAX / 64;
 constexpr int REG_T = 16;                   // entries of a row of A' in registers (longer rows: the rest from memory)
 
 // ---- reductions -----------------------------------------------------------------
@@ -48,11 +48,11 @@ __device__ __forceinline__ double wave_reduce(int kind, double v)
     return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-// Sum (bit j of MAXM clear) or maximum (set) of NR values over the
-// workgroup, in a fixed order, in every thread.  The caller puts a barrier
+// Sum (bit j of MAXM clear) or maximum (set) of NR values over the workgroup
+// of T threads, in a fixed order, in every thread.  The caller puts a barrier
 // between two reductions' uses of `lds` (any barrier after this returns).
 constexpr int RED_SLOTS = 8;
-template <int NR, unsigned MAXM>
+template <int T, int NR, unsigned MAXM>
 __device__ __forceinline__ void wg_sum(double (&v)[NR], double* lds)
 {
     static_assert(NR <= RED_SLOTS, "the buffer holds RED_SLOTS slots");
@@ -66,7 +66,7 @@ __device__ __forceinline__ void wg_sum(double (&v)[NR], double* lds)
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
         double r = lds[j];
-        for (int w = 1; w < WAVES; ++w) r = rcomb(((MAXM >> j) & 1u) ? R_MAX : R_SUM, r, lds[w * NR + j]);
+        for (int w = 1; w < T / 64; ++w) r = rcomb(((MAXM >> j) & 1u) ? R_MAX : R_SUM, r, lds[w * NR + j]);
         v[j] = uniform(r);
     }
 }
@@ -75,7 +75,7 @@ __device__ __forceinline__ void wg_sum(double (&v)[NR], double* lds)
 // order of a workgroup of 256 threads (batch.hip's norm kernel and default
 // shape), in every thread: the weight's update and the norms, from which all
 // step sizes come, keep their bits, so that no operand's FP32 rounding turns.
-// buf: 1024 doubles.  Two barriers and one more before buf is used again.
+// buf: a double per thread.  Two barriers and one more before buf is used again.
 __device__ __forceinline__ double sumsq_256(double v, int len, double* buf, double* lds)
 {
     buf[threadIdx.x] = v;
@@ -171,8 +171,8 @@ struct ClosedArgs {
 // takes registers from the iteration, whose matrix rows are then spilled and
 // reloaded in every step (5.4 us instead of 3.7 on a 748-variable instance).
 // It reads the kernel's arguments from their segment.
-// GEN: Q is not diagonal.
-template <bool F32, bool GEN>
+// GEN: Q is not diagonal.  T: threads.
+template <bool F32, bool GEN, int T>
 __device__ __attribute__((noinline)) int one_cu_check(unsigned long long args, int b, double* red, ClosedState* s)
 {
     const unsigned lo = (unsigned)uniform_int((int)(args & 0xffffffffull)), hi = (unsigned)uniform_int((int)(args >> 32));
@@ -208,7 +208,7 @@ __device__ __attribute__((noinline)) int one_cu_check(unsigned long long args, i
         a[0] = fabs(aty);
     }
     __syncthreads();
-    wg_sum<4, 3u>(a, red);
+    wg_sum<T, 4, 3u>(a, red);
     // A x_T, A d: violation (max), p(y), violation of A d (max)
     double c[3] = {0.0, 0.0, 0.0};
     if (yon) {
@@ -223,7 +223,7 @@ __device__ __attribute__((noinline)) int one_cu_check(unsigned long long args, i
         if (later && unb) c[2] = fabs(ad - projRec(ad, lc, uc));
     }
     __syncthreads();
-    wg_sum<3, 5u>(c, red);
+    wg_sum<T, 3, 5u>(c, red);
     // Q x_T, Q d and the reduced cost: maxima 0, 1, 5 and 6, the rest sums
     double e[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (xon) {
@@ -249,7 +249,7 @@ __device__ __attribute__((noinline)) int one_cu_check(unsigned long long args, i
         e[6] = fabs(qv);
     }
     __syncthreads();
-    wg_sum<7, (1u << 0) | (1u << 1) | (1u << 5) | (1u << 6)>(e, red);
+    wg_sum<T, 7, (1u << 0) | (1u << 1) | (1u << 5) | (1u << 6)>(e, red);
 
     const double rp = c[0] / in.bscale;
     double sd = e[1] > a[0] ? e[1] : a[0];
@@ -284,7 +284,7 @@ __device__ __attribute__((noinline)) int one_cu_check(unsigned long long args, i
                   (double)t >= P.rs_art * (double)k;
     }
     if (uniform_int(restart)) {
-        double* buf = red + RED_SLOTS * WAVES;   // the first operand's space
+        double* buf = red + RED_SLOTS * (T / 64);   // the first operand's space
         __syncthreads();
         mx = sqrt(sumsq_256(xon ? xt[tid] - B.xa[vi] : 0.0, in.n, buf, red));
         __syncthreads();
@@ -335,8 +335,8 @@ __device__ __forceinline__ double div_by(double a, double b, double r)
     return isfinite(c) ? c : a / b;
 }
 
-// workgroups of a launch: one per CU at most
-inline int one_cu_grid(int count)
+// workgroups of a launch: `per` to a CU at most
+inline int one_cu_grid(int count, int per = 1)
 {
     static const int cus = [] {
         int dev = 0, c = 0;
@@ -345,7 +345,7 @@ inline int one_cu_grid(int count)
             return c;
         return 256;
     }();
-    return count < cus ? count : cus;
+    return count < per * cus ? count : per * cus;
 }
 
 }  // namespace pdhcg

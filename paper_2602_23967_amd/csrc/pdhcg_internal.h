@@ -261,11 +261,11 @@ struct BatchParams {
 
 struct BatchDev {
     int count = 0;
-    int* queue = nullptr;                       // work counters (instances taken): rest, closed, general
+    int* queue = nullptr;                       // work counters (instances taken): rest, closed, general, small
     // queue position -> instance, for the kernels of batch.hip, closed.hip
-    // and general.hip
-    int rest_count = 0, closed_count = 0, general_count = 0;
-    const int *rest_list = nullptr, *closed_list = nullptr, *general_list = nullptr;
+    // and (two sizes of workgroup) general.hip
+    int rest_count = 0, closed_count = 0, general_count = 0, small_count = 0;
+    const int *rest_list = nullptr, *closed_list = nullptr, *general_list = nullptr, *small_list = nullptr;
     const int *voff = nullptr, *roff = nullptr; // count + 1 each
     const int *arp = nullptr, *acol = nullptr;  // A, global indices
     const double* aval = nullptr;
@@ -313,8 +313,16 @@ hipError_t launch_batch_solve(const BatchDev& B, const BatchParams& P, int shape
 constexpr int ONE_CU_MAX = 1024;
 constexpr int ONE_CU_REG_Q = 16;     // entries of a row of Q in registers
 constexpr int ONE_CU_REST_Q = 5632;  // LDS places for the others (64 rows of a wave as long as the longest)
+constexpr int ONE_CU_SMALL = 256;    // variables and rows of an instance that shares the CU with three others
+constexpr int ONE_CU_SMALL_Q = 3200; // and LDS places for its rows of Q
+// With more rows than that an instance has a CU from so many variables on: a
+// batch that fills the chip is slower with few variables on a whole CU (1024
+// instances, 128 iterations, four to a CU in the general kernel and here: 128
+// variables and 400 rows 9.1 and 11.0 ms, 256 and 512 12.7 and 11.0).
+constexpr int ONE_CU_MANY_ROWS = 224;
 hipError_t launch_closed_solve(const BatchDev& B, const BatchParams& P, hipStream_t s);
 hipError_t launch_general_solve(const BatchDev& B, const BatchParams& P, hipStream_t s);
+hipError_t launch_small_solve(const BatchDev& B, const BatchParams& P, hipStream_t s);
 hipError_t launch_closed_norm(const BatchDev& B, double tol, long long max_iter, double* out, hipStream_t s);
 // dst[i] = (float)src[i]
 hipError_t launch_to_f32(const double* src, float* dst, long long len, hipStream_t s);
