@@ -51,36 +51,6 @@ constexpr int LDS_FIXED = LDS_RED + 2 * LDS_OP + LDS_STATE + LDS_MISC;
 template <class T>
 constexpr int mat_places() { return (int)((LDS_ALL - LDS_FIXED - lds_own<T>()) * 8 / (sizeof(T) + 2)) & ~63; }
 
-// entries of the longest row of the wave (uniform)
-__device__ __forceinline__ int wave_longest(int len)
-{
-    int most = 0;
-    while (__ballot(len > most) != 0ull) ++most;
-    return uniform_int(most);
-}
-
-// A wave's rows of A in LDS: `wide` entries of each of its 64 rows from place
-// `base` on, entry after entry.  The waves' places follow each other; where
-// the space ends, the rest of the rows' entries is read from memory.
-struct WaveMat {
-    int base, wide;
-};
-template <class T>
-__device__ __forceinline__ WaveMat place_rows(int most, int* widths)
-{
-    const int wave = uniform_int(threadIdx.x >> 6);
-    if ((threadIdx.x & 63) == 0) widths[wave] = most;
-    __syncthreads();
-    int base = 0;
-    for (int w = 0; w < wave; ++w) base += 64 * widths[w];
-    WaveMat p;
-    p.base = uniform_int(base < mat_places<T>() ? base : mat_places<T>());
-    const int fit = (mat_places<T>() - p.base) / 64;
-    p.wide = uniform_int(most < fit ? most : fit);
-    __syncthreads();
-    return p;
-}
-
 // Loads the first CAP entries of the thread's row (a, len) into registers:
 // values, and offsets in bytes into the operand.  A missing entry is 0 times
 // the operand's entry `zero`, a zero, so a wave's rows need no masks.
@@ -124,7 +94,7 @@ __device__ __forceinline__ void load_row(int a, int len, const T* val, const uns
 
 // the same for a wave's rows of A in LDS
 template <class T>
-__device__ __forceinline__ void load_mat(WaveMat p, int a, int len, const T* val, const unsigned short* c16, const int* c32,
+__device__ __forceinline__ void load_mat(Share p, int a, int len, const T* val, const unsigned short* c16, const int* c32,
                                          int first, int zero, T* lv, unsigned short* lo)
 {
     const int at = p.base + (threadIdx.x & 63);
@@ -170,7 +140,7 @@ __device__ __forceinline__ T dot_row(const T (&v)[CAP], const unsigned (&o)[CAP]
 
 // row of A in LDS times the operand x, in row order
 template <class T>
-__device__ __forceinline__ T dot_mat(WaveMat p, int most, const T* lv, const unsigned short* lo, int a, int len,
+__device__ __forceinline__ T dot_mat(Share p, int most, const T* lv, const unsigned short* lo, int a, int len,
                                      const T* val, const unsigned short* c16, const int* c32, int first, const T* x)
 {
     const int at = p.base + (threadIdx.x & 63);
@@ -226,7 +196,7 @@ __global__ __launch_bounds__(REG_MAX) void k_closed_solve(BatchDev B, BatchParam
         const int ta = xon ? B.trp[vi] : 0, tl = xon ? B.trp[vi + 1] - ta : 0;
         const int aa = yon ? B.arp[ri] : 0, al = yon ? B.arp[ri + 1] - aa : 0;
         const int tmost = wave_longest(tl), amost = wave_longest(al);
-        const WaveMat wm = place_rows<T>(amost, misc + 16);
+        const Share wm = share<REG_MAX>(amost, 0, mat_places<T>(), misc + 16);
         load_mat<T>(wm, aa, al, aval, B.acol16, B.acol, v0, n, lav, lao);
         double x = 0.0, y = 0.0;
         if (xon) {
@@ -436,7 +406,7 @@ __global__ __launch_bounds__(REG_MAX) void k_closed_norm(BatchDev B, double tol,
         const int ta = xon ? B.trp[v0 + tid] : 0, tl = xon ? B.trp[v0 + tid + 1] - ta : 0;
         const int aa = yon ? B.arp[r0 + tid] : 0, al = yon ? B.arp[r0 + tid + 1] - aa : 0;
         const int tmost = wave_longest(tl), amost = wave_longest(al);
-        const WaveMat wm = place_rows<double>(amost, misc + 16);
+        const Share wm = share<REG_MAX>(amost, 0, mat_places<double>(), misc + 16);
         load_mat<double>(wm, aa, al, B.aval, B.acol16, B.acol, v0, n, lav, lao);
         for (int i = tid; i < 2 * LDS_OP; i += REG_MAX) sh[LDS_RED + i] = 0.0;
         double tv[REG_T];

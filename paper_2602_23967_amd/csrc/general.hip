@@ -122,39 +122,6 @@ __device__ __forceinline__ void step_sum(double (&v)[4], bool live, double* lds)
     }
 }
 
-// entries of the longest row of the wave (uniform)
-__device__ __forceinline__ int longest(int len)
-{
-    int most = 0;
-    while (__ballot(len > most) != 0ull) ++most;
-    return uniform_int(most);
-}
-
-// the wave's share of the places [first, total): `base` and how many entries
-// of each of its 64 rows fit; the waves' shares follow each other up to `end`
-struct Share {
-    int base, wide, end;
-};
-template <int T>
-__device__ __forceinline__ Share share(int want, int first, int total, int* widths)
-{
-    const int wave = uniform_int(threadIdx.x >> 6);
-    if ((threadIdx.x & 63) == 0) widths[wave] = want;
-    __syncthreads();
-    int base = first, end = first;
-    for (int w = 0; w < T / 64; ++w) {
-        if (w == wave) base = end;
-        end += 64 * widths[w];
-    }
-    Share p;
-    p.base = uniform_int(base < total ? base : total);
-    p.end = uniform_int(end < total ? end : total);
-    const int fit = (total - p.base) / 64;
-    p.wide = uniform_int(want < fit ? want : fit);
-    __syncthreads();
-    return p;
-}
-
 // entries [from, from + wide) of the thread's row to the wave's places;
 // deal: place of a column; a missing entry is 0 times the operand's zero
 __device__ __forceinline__ void fill(Share p, int a, int len, int from, const double* val, const unsigned short* c16,
@@ -372,7 +339,7 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_g
         const int qa = xon ? B.qrp[vi] : 0, ql = xon ? B.qrp[vi + 1] - qa : 0;
         const int ta = xon ? B.trp[vi] : 0, tl = xon ? B.trp[vi + 1] - ta : 0;
         const int aa = yon ? B.arp[ri] : 0, al = yon ? B.arp[ri + 1] - aa : 0;
-        const int qmost = longest(ql), amost = longest(al);
+        const int qmost = wave_longest(ql), amost = wave_longest(al);
         const bool live = uniform_int(tid & ~63) < n, any = uniform_int(tid & ~63) < (n > m ? n : m);
         RowQ Q;
         Q.most = qmost;
@@ -584,7 +551,7 @@ __global__ __launch_bounds__(REG_MAX) void k_single_solve(DevState S, CoopRun R)
     const int qa = xon ? S.Q.rowptr[vi] : 0, ql = xon ? S.Q.rowptr[vi + 1] - qa : 0;
     const int ta = xon ? S.AT.rowptr[vi] : 0, tl = xon ? S.AT.rowptr[vi + 1] - ta : 0;
     const int aa = yon ? S.A.rowptr[ri] : 0, al = yon ? S.A.rowptr[ri + 1] - aa : 0;
-    const int qmost = longest(ql), amost = longest(al);
+    const int qmost = wave_longest(ql), amost = wave_longest(al);
     const Share qs = share<T>(qmost > REG_Q ? qmost - REG_Q : 0, 0, L::PLACES, misc + 16);
     const Share as = share<T>(amost, qs.end, L::PLACES, misc + 16);
     fill(qs, qa, ql, REG_Q, S.Q.val, nullptr, S.Q.col, 0, place, n, lv, lo);

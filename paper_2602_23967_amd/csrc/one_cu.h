@@ -93,6 +93,41 @@ __device__ __forceinline__ double sumsq_256(double v, int len, double* buf, doub
     return uniform(r);
 }
 
+// ---- a workgroup's rows in LDS -----------------------------------------------------
+
+// entries of the longest row of the wave (uniform)
+__device__ __forceinline__ int wave_longest(int len)
+{
+    int most = 0;
+    while (__ballot(len > most) != 0ull) ++most;
+    return uniform_int(most);
+}
+
+// the wave's share of the places [first, total): `base` and how many entries
+// of each of its 64 rows fit; the waves' shares follow each other up to `end`
+struct Share {
+    int base, wide, end;
+};
+template <int T>
+__device__ __forceinline__ Share share(int want, int first, int total, int* widths)
+{
+    const int wave = uniform_int(threadIdx.x >> 6);
+    if ((threadIdx.x & 63) == 0) widths[wave] = want;
+    __syncthreads();
+    int base = first, end = first;
+    for (int w = 0; w < T / 64; ++w) {
+        if (w == wave) base = end;
+        end += 64 * widths[w];
+    }
+    Share p;
+    p.base = uniform_int(base < total ? base : total);
+    p.end = uniform_int(end < total ? end : total);
+    const int fit = (total - p.base) / 64;
+    p.wide = uniform_int(want < fit ? want : fit);
+    __syncthreads();
+    return p;
+}
+
 // ---- one instance ---------------------------------------------------------------
 
 // its ranges and per-instance values (the same in every thread)
