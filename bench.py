@@ -221,6 +221,23 @@ def batch_bytes(q, iters, vb=12, bb=16):
     return per_iter * iters
 
 
+def one_cu_bytes(q, iters, check_every, mixed, cb, bb):
+    """Algorithmic bytes of one closed-form instance in the kernel that keeps
+    it on a CU (cb B per column index, bb per variable's box).  Nothing is
+    read in an iteration.  Once: A (placed in LDS).  Per check: A' in FP64 for
+    A'y_T and A'ytil, A for A x_T, with x, c, q, the box, the row bounds, y_T
+    and ytil, and A'y_T written (mixed: A x_T too).  Per stretch of iterations
+    up to a check: the thread's row of A' (vb B per value), c, q, the box, the
+    anchors and the row bounds (mixed: the reference point and its products)
+    read, x_T, y_T and ytil written."""
+    vb = 4 if mixed else 8
+    checks = -(-iters // check_every)
+    once = (vb + cb) * q.nnz_A + 4 * (q.n + q.m + 2)
+    check = 2 * (8 + cb) * q.nnz_A + (8 * 4 + bb) * q.n + 8 * 4 * q.m + (8 * q.m if mixed else 0)
+    stretch = (vb + cb) * q.nnz_A + (8 * 4 + bb) * q.n + 8 * 5 * q.m + (16 * (q.n + q.m) if mixed else 0)
+    return once + checks * (check + stretch)
+
+
 def main_batch(args, torch, P, I):
     t = time.perf_counter()
     qs = [I.mpc(i) for i in range(args.count)]
@@ -275,7 +292,13 @@ def main_batch(args, torch, P, I):
                              "lb": np.concatenate([np.full(q.n, -np.inf) if q.lb is None else q.lb for q in qs]),
                              "ub": np.concatenate([np.full(q.n, np.inf) if q.ub is None else q.ub for q in qs])})
     bb = bound_bytes(whole)
-    nbytes = sum(batch_bytes(q, it, (4 if mixed else 8) + col_b, bb) for q, it in zip(qs, iters))
+    # the two default shapes keep an instance of up to 1024 variables and rows
+    # on a CU, the others run the general batched kernel
+    one_cu = [shape in (P.qp_batch_default_shape(False), P.qp_batch_default_shape(True)) and max(q.n, q.m) <= 1024
+              for q in qs]
+    nbytes = sum(one_cu_bytes(q, it, params.check_every, mixed, col_b, bb) if cu else
+                 batch_bytes(q, it, (4 if mixed else 8) + col_b, bb) for q, it, cu in zip(qs, iters, one_cu))
+    kernel = " + ".join([k for k, on in (("k_closed_solve", any(one_cu)), ("k_batch_solve", not all(one_cu))) if on])
     kernel_s = float(np.median(lat))
     bs.close()
     # the same instances one at a time through the single-QP path, FP64
@@ -315,7 +338,7 @@ def main_batch(args, torch, P, I):
         "iterations": {"mean": float(np.mean(iters)), "max": int(np.max(iters))},
         "roofline": {"bound": "hbm", "achieved": nbytes / kernel_s / 1e9, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": nbytes / kernel_s / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "k_batch_solve", "bytes_per_launch": nbytes, "avg_us": kernel_s * 1e6},
+                     "kernel": kernel, "bytes_per_launch": nbytes, "avg_us": kernel_s * 1e6},
         "one_at_a_time": {"value": 1.0 / float(np.mean(one)), "unit": "QPs solved/s",
                           "sample": f"first {len(one)} instances, qp_solve each (FP64, same GPU)"},
         "schedule": sched,
@@ -712,8 +735,12 @@ def main_single(args, torch, P, I):
     log(f"generated {q.name}: n={q.n} m={q.m} nnz(Q)={q.nnz_Q} nnz(A)={q.nnz_A} "
         f"in {time.perf_counter() - t:.1f}s")
     h = P.qp_create_from(q)
-    params = P.qp_params_default(tol=args.tol, timing=args.timing, inner_lag=args.lag,
+    # the n = 1000 QP runs whole iterations in one launch, which a solve that
+    # times its kernels does not: timed as a default solve, and once more
+    # launch by launch for the kernels' times
+    params = P.qp_params_default(tol=args.tol, timing=0 if small else args.timing, inner_lag=args.lag,
                                  max_iter=args.max_iter)
+    by_launch = None
     try:
         for w in range(args.warmup):
             st = P.qp_solve_ex(h, params)
@@ -732,6 +759,10 @@ def main_single(args, torch, P, I):
                 f"{info['r_gap']:.1e})")
         torch.cuda.synchronize()
         elapsed = time.perf_counter() - t_start
+        if small and args.timing > 0:
+            P.qp_solve_ex(h, P.qp_params_default(tol=args.tol, timing=args.timing, inner_lag=args.lag,
+                                                 max_iter=args.max_iter))
+            by_launch = P.qp_result(h, q.n, q.m)[3]
     finally:
         _, x, y, info = P.qp_result(h, q.n, q.m)
         P.qp_destroy(h)
@@ -755,11 +786,12 @@ def main_single(args, torch, P, I):
         if tr.get("kernels_digest") == kernels_digest():
             traffic = tr.get("bytes_per_launch")
     kern = {}
+    timed_infos = [by_launch] if by_launch else infos
     for j, name in enumerate(P.FAMILIES):
-        tj = sum(i["fam_timed"][j] for i in infos)
+        tj = sum(i["fam_timed"][j] for i in timed_infos)
         if tj:
-            kern[name] = {"avg_us": round(1e3 * sum(i["fam_ms"][j] for i in infos) / tj, 3),
-                          "launches_per_solve": infos[-1]["fam_launches"][j]}
+            kern[name] = {"avg_us": round(1e3 * sum(i["fam_ms"][j] for i in timed_infos) / tj, 3),
+                          "launches_per_solve": timed_infos[-1]["fam_launches"][j]}
     # the product's random gathers (one per nonzero) against the device's
     # measured gather rate for the same vector length and part keying: the
     # bound this product actually meets (outside the timed region)
@@ -798,8 +830,7 @@ def main_single(args, torch, P, I):
                        "inner_per_s": infos[-1]["inner_iterations"] / np.median(lat)},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": (achieved / HBM_PEAK_GBS) if achieved else None, "traffic": traffic,
-                     "kernel": ("inner H p product (k_spmv<EpiStepA>)" if small else
-                                "inner H p product (k_spmv<EpiStepA> + k_rows<EpiStepA>)"),
+                     "kernel": "inner H p product (k_spmv<EpiStepA> + k_rows<EpiStepA>)",
                      "bytes_per_launch": nbytes, "avg_us": avg_us, "timed_launches": timed,
                      "launches": launches, "active_launches": active},
         "gather_roofline": gather,
@@ -812,15 +843,27 @@ def main_single(args, torch, P, I):
                            "note": "qp_create from host arrays + qp_solve + qp_result, one problem"},
     }
     if small:
-        # launch-bound: the latency of one iteration is the figure that matters
+        # one launch runs the iterations up to the next check, with the problem
+        # on one CU: what it cannot do without is the problem and its vectors
+        # once; the latency of one iteration is the figure that matters
         med = float(np.median(lat))
-        fam_us = {k: v["avg_us"] for k, v in kern.items()}
+        n_launch = max(infos[-1]["checks"], 1)
+        nbytes = 12 * (q.nnz_Q + 2 * q.nnz_A) + 4 * (2 * q.n + q.m + 3) + (8 * 11 + bound_bytes(q)) * q.n + 8 * 7 * q.m
+        achieved = nbytes * n_launch / med / 1e9
+        out["roofline"] = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                           "frac": achieved / HBM_PEAK_GBS, "traffic": None, "kernel": "k_single_solve",
+                           "bytes_per_launch": nbytes, "avg_us": 1e6 * med / n_launch, "launches": n_launch,
+                           "note": "bound by instruction issue on one CU; avg_us: solve time per launch, checks included"}
         out["latency_us"] = {
             "per_outer_iteration": 1e6 * med / max(infos[-1]["iterations"], 1),
-            "per_inner_step_kernels": sum(fam_us.get(k, 0.0) for k in ("dir", "spmv_hp", "update")),
-            "note": ("per_outer_iteration = solve wall time / outer iterations (inner steps included); "
-                     "per_inner_step_kernels = event-timed main kernels of one inner step (direction, H p, "
-                     "update; finishing kernels and launch gaps not included)")}
+            "per_inner_step": 1e6 * med / max(infos[-1]["inner_iterations"], 1),
+            "note": "solve wall time over outer iterations and over inner steps, all else included"}
+        if by_launch:
+            out["launch_by_launch"] = {
+                "value": 1.0 / by_launch["solve_seconds"], "unit": "QPs solved/s", "solve_s": by_launch["solve_seconds"],
+                "per_inner_step_kernels_us": sum(kern.get(k, {"avg_us": 0.0})["avg_us"] for k in ("dir", "spmv_hp", "update")),
+                "note": "one solve that times its kernels, which takes the launch-by-launch path (\"kernels\": its "
+                        "event-timed main kernels; finishing kernels and launch gaps not included)"}
     if not args.no_cpu_baseline:
         if small:
             out["cpu_baseline"] = cpu_small(q, args.tol)
@@ -839,7 +882,7 @@ def summary(out):
     """The figures of a workload's line that the default run attaches for
     the other workloads (measured in the same run)."""
     keep = ("value", "unit", "ms_per_step", "steps", "dtype", "solved", "solved_count", "requests", "iterations",
-            "latency_s", "latency_us", "fp64_plain", "one_at_a_time", "error_vs_fp64", "oracle_verified",
+            "latency_s", "latency_us", "launch_by_launch", "fp64_plain", "one_at_a_time", "error_vs_fp64", "oracle_verified",
             "instance_times_ms")
     d = {k: out[k] for k in keep if k in out}
     d["workload"] = out["config"]["workload"]
@@ -852,7 +895,7 @@ def summary(out):
 def run_secondary(args, torch, P, I):
     """The other workloads' lines in the default run: the factor portfolio
     (mixed precision, with its FP64 solve), the 4096-instance MPC batch
-    (mixed, autotuned), the n = 1000 QP (FP64, launch-bound) and the served
+    (mixed, autotuned), the n = 1000 QP (FP64, latency-bound) and the served
     stream (mixed), each timed as its own --workload run would be, without
     CPU baselines; the served stream keeps its oracle check of a sample
     (unless --no-cpu-baseline) with shorter budgets for that check and for
