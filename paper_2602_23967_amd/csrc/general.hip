@@ -16,7 +16,9 @@
 // that fills the chip was slower than in the general kernel, which kept four
 // instances on a CU (128 iterations of 1024 random QPs, general kernel, 1024
 // threads and 256: 128 variables 6.2, 8.1 and 2.4 ms, 256 9.6, 8.7 and 3.0;
-// 48 of them 4.4, 2.1 and 1.6, 4.8, 2.3 and 1.8).
+// 48 of them 4.4, 2.1 and 1.6, 4.8, 2.3 and 1.8).  Both sizes of workgroup
+// make the same results to the bit: the waves that only the larger one has
+// add zeros at the end of every sum.
 //
 // The variables are dealt to the threads by the length of their row of Q,
 // longest first: a wave's product takes as long as its longest row, so in
@@ -723,6 +725,8 @@ hipError_t launch_general_solve(const BatchDev& B, const BatchParams& P, hipStre
     k_general_solve<REG_MAX><<<one_cu_grid(B.general_count), REG_MAX, 0, s>>>(B, P);
     return hipGetLastError();
 }
+
+int one_cu_places() { return one_cu_grid(1 << 30); }
 
 hipError_t launch_small_solve(const BatchDev& B, const BatchParams& P, hipStream_t s)
 {

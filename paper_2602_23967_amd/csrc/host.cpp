@@ -1597,7 +1597,15 @@ int batch_launch(qp_batch* bt, const qp_params* params)
     const bool split = bt->shape == BATCH_SHAPE_DEFAULT || bt->shape == BATCH_SHAPE_GENERAL_DEFAULT;
     const int nc = split ? bt->nclosed : 0;
     const bool inner = split && p.precision == QP_PRECISION_FP64;
-    const int ng = inner ? bt->ngeneral : 0, ns = inner ? bt->nsmall : 0;
+    int ng = inner ? bt->ngeneral : 0, ns = inner ? bt->nsmall : 0;
+    // Small instances beside larger ones, all with a CU of their own: one
+    // launch, which then takes as long as its largest instance (the same
+    // results; two launches do not overlap where their streams share a
+    // hardware queue: 24 random QPs of 200 to 1000 variables 25 ms for 19).
+    if (ng > 0 && ng + ns <= one_cu_places()) {
+        ng += ns;
+        ns = 0;
+    }
     const int* list = bt->dsplit[bt->order];
     bt->B.closed_count = nc;
     bt->B.closed_list = list;

@@ -323,6 +323,7 @@ constexpr int ONE_CU_MANY_ROWS = 224;
 hipError_t launch_closed_solve(const BatchDev& B, const BatchParams& P, hipStream_t s);
 hipError_t launch_general_solve(const BatchDev& B, const BatchParams& P, hipStream_t s);
 hipError_t launch_small_solve(const BatchDev& B, const BatchParams& P, hipStream_t s);
+int one_cu_places();   // instances that have a CU of their own at the same time
 hipError_t launch_closed_norm(const BatchDev& B, double tol, long long max_iter, double* out, hipStream_t s);
 // dst[i] = (float)src[i]
 hipError_t launch_to_f32(const double* src, float* dst, long long len, hipStream_t s);

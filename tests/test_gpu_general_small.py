@@ -42,6 +42,23 @@ def test_small_instances(torch, n, m, q_row, a_row):
             assert np.abs(g.y - r.y).max() <= 1e-9 * (1.0 + np.abs(r.y).max())
 
 
+def test_both_workgroups_make_the_same_bits(torch):
+    """Alone they take 256 threads; beside a larger instance 1024."""
+    qs = [_qp(n, m, q, a, 5) for n, m, q, a in
+          [(2, 1, 0, 1), (64, 64, 63, 9), (65, 0, 20, 1), (128, 256, 34, 30), (255, 255, 9, 5), (256, 128, 24, 20)]]
+    for kw in (dict(max_iter=70, check_every=7, tol=1e-13), dict(tol=1e-7)):
+        got = []
+        for extra in ([], [_qp(400, 100, 9, 5, 6)]):
+            with P.BatchSolver(qs + extra) as bs:
+                bs.solve(**kw)
+                got.append([bs.result(i) for i in range(len(qs))])
+        for q, a, b in zip(qs, *got):
+            assert a.status == b.status, q.name
+            for k in ("iterations", "inner_iterations", "restarts", "omega", "r_primal", "r_dual", "primal_obj"):
+                assert a.info[k] == b.info[k], (q.name, k)
+            assert np.array_equal(a.x, b.x) and np.array_equal(a.y, b.y), q.name
+
+
 def test_more_instances_than_the_chip_holds(torch):
     kinds = [_qp(n, m, 5, 3, 7) for n, m in [(20, 10), (100, 40), (250, 120)]]
     kw = dict(max_iter=70, check_every=7, tol=1e-13)
