@@ -340,8 +340,10 @@ int qp_batch_solve_static(int64_t count, const int64_t* var_off, const int64_t* 
  * terms by the workgroup size), and each shape is deterministic.  Under the
  * two default shapes an instance with at most 1024 variables and rows gets a
  * whole CU and a workgroup of 1024 threads, which holds its matrices in
- * registers and LDS; with a non-diagonal Q in FP64 only, and if the CU holds
- * its rows of Q. */
+ * registers and LDS; with a non-diagonal Q in FP64 only, if the CU holds its
+ * rows of Q, and with more than 256 rows only from 224 variables on.  (Four
+ * instances with a non-diagonal Q and at most 256 variables and rows may
+ * share a CU.)  An instance's result never depends on the others. */
 
 /* Number of compiled shapes, and shape i's threads per workgroup, LDS
  * doubles and the waves per SIMD its register allocation leaves room for

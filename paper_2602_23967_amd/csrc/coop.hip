@@ -25,11 +25,11 @@
 //
 // Progress.  The rows are cut into slices that do not depend on W; workgroup i
 // of W takes slices i, i + W, ..., at least one of each matrix, so that it
-// posts in every round (coop_rounds.h: why it has to).  W is how many workgroups had
-// started when the first of them closed the list (all of the grid, or those
-// that came within REG_WAIT_US): nobody waits for a workgroup that has not
-// started, so kernels of other streams cannot block the group, and the
-// result does not depend on W.
+// posts in every round (coop_rounds.h: why it has to).  W is how many
+// workgroups had started when the first of them closed the list (all of the
+// grid, or those that came within REG_WAIT_TICKS): nobody waits for a
+// workgroup that has not started, so kernels of other streams cannot block the
+// group, and the result does not depend on W.
 //
 // FP64 only.  The FP64 sums differ from the launch-by-launch path's in their
 // last bits, which moves a solve's result by 1e-15; in mixed precision such a

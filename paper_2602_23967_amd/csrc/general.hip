@@ -526,9 +526,9 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(4))) void k_g
 //
 // The same for a single problem: whole iterations up to the next check, as
 // coop.hip's kernel makes them with a group of workgroups (the gradient
-// updated from the previous subproblem's), whose rounds cost 5 us each: a
-// random QP with n = 1000 to its tolerance takes 80 ms here, about 140 there
-// and 363 launch by launch.
+// updated from the previous subproblem's), whose rounds cost 5 us each: the
+// random QP with n = 1000, instance 0, to 1e-6 (17,990 inner steps) takes 98 ms
+// here, 5.5 us a step, and 0.50 s launch by launch; there a step took 10.9 us.
 __global__ __launch_bounds__(REG_MAX) void k_single_solve(DevState S, CoopRun R)
 {
     constexpr int T = REG_MAX;

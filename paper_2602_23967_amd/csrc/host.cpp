@@ -265,8 +265,9 @@ int coop_create(qp_handle* h, const int64_t* qp, const int64_t* ap, const int64_
     if (h->qkind != 2 || S.k > 0 || S.Q.nparts > 1 || S.A.nparts > 1 || S.AT.nparts > 1) return 0;
     if (longest_row(n, qp) > COOP_ROW || longest_row(m, ap) > COOP_ROW || longest_row(n, tp) > COOP_COL) return 0;
     if (one_cu_fits(n, m, qp)) {
-        // (n = 1000 to its tolerance: 363 ms launch by launch, about 140
-        // with a group of workgroups, 80 on one CU)
+        // (random QP with n = 1000, instance 0, to 1e-6, 17,990 inner steps:
+        // 0.50 s launch by launch, 0.098 on one CU, 5.5 us a step where a group
+        // of workgroups took 10.9)
         h->single = 1;
         return 0;
     }

@@ -291,7 +291,8 @@ bool coop_layout(int64_t n, const int64_t* qp, int64_t m, const int64_t* ap, int
     // Slices of 256 rows up to 128 of them, then of 512: every workgroup reads
     // every slice's words in a round (random QPs, 128 iterations, slices of
     // 256 and of 512: n = 3000 13.2 and 17.0 ms, n = 8000 16.0 and 18.6, n =
-    // 20,011, just past the line, 23.4 and 24.1, n = 50,000 56.3 and 38.5).
+    // 20,011, just past the line, 23.4 and 24.1, n = 50,000 56.3 and 38.5: the
+    // two cross between the last two, and near there the line costs 3 %).
     L.threads = 256;
     L.q = coop_slices(n, qp, L.threads);
     if ((int)L.q.size() > 128) L.q = coop_slices(n, qp, L.threads = 512);

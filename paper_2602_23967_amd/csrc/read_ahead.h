@@ -13,8 +13,8 @@
 namespace pdhcg {
 
 // A copy to the host takes 25 us however short it is, and two for each of
-// 4096 MPC problems were 213 ms after a solve of 54; in blocks of READ_AHEAD
-// doubles fetching them all is 53 ms, most of it the caller's.  Any other
+// 4096 MPC problems were 213 ms after a solve of 23; in blocks of READ_AHEAD
+// doubles fetching them all is 44 ms, most of it the caller's.  Any other
 // order copies what is asked for alone.
 constexpr int64_t READ_AHEAD = 1 << 18;   // doubles in a block at most (2 MiB)
 
